@@ -384,7 +384,6 @@ void pvs_state::release_scan_buffers() {
     dev_free(pairs);
     dev_free(keys);
     dev_free(keys_tmp);
-    dev_free(packed);
     if (h_scanq) (void)hipHostFree(h_scanq);
     if (h_counts) (void)hipHostFree(h_counts);
     if (h_packed) (void)hipHostFree(h_packed);
@@ -400,7 +399,7 @@ void pvs_state::release_scan_buffers() {
 // Move the scan buffers between a state and an index's spare slot.
 #define PVS_BUFFER_FIELDS(X)                                                                 \
     X(buf_nq) X(buf_sample) X(scanq) X(counts) X(sample_lo) X(sample_hi) X(qfrag) X(pool_cap) \
-    X(pairs) X(keys) X(keys_tmp) X(packed) X(h_scanq) X(h_counts)    \
+    X(pairs) X(keys) X(keys_tmp) X(h_scanq) X(h_counts)    \
     X(h_packed) X(h_packed_cap)
 
 static void adopt_buffers(pvs_state* st, ScanBuffers& b) {
@@ -441,7 +440,6 @@ static void donate_buffers(pvs_state* st, ScanBuffers& b) {
     st->pairs = nullptr;
     st->keys = nullptr;
     st->keys_tmp = nullptr;
-    st->packed = nullptr;
     st->h_scanq = nullptr;
     st->h_counts = nullptr;
     st->h_packed = nullptr;
@@ -456,7 +454,6 @@ static void free_buffers(ScanBuffers& b) {
     dev_free(b.pairs);
     dev_free(b.keys);
     dev_free(b.keys_tmp);
-    dev_free(b.packed);
     if (b.h_scanq) (void)hipHostFree(b.h_scanq);
     if (b.h_counts) (void)hipHostFree(b.h_counts);
     if (b.h_packed) (void)hipHostFree(b.h_packed);
@@ -464,8 +461,7 @@ static void free_buffers(ScanBuffers& b) {
 }
 
 // Per-query scan buffers for nq queries and samples of sample_ld rows.
-// counts layout: [cert nq][fail nq][offs nq + 1][unused 1]
-// [rescore chunk base kSub + 1], then from pair_counts_at(nq) the kSub append
+// counts layout: [cert nq][fail nq][unused nq + 2][rescore chunk base kSub + 1], then from pair_counts_at(nq) the kSub append
 // counters of the pair pool, from reads_counts_at(nq) the kSub row-load
 // counters of rescoring, kCntStride ints apart, and from evals_counts_at(nq)
 // the records of each query.  h_counts mirrors it.
@@ -518,13 +514,11 @@ static int ensure_pool(pvs_state* st, int64_t slots) {
     dev_free(st->pairs);
     dev_free(st->keys);
     dev_free(st->keys_tmp);
-    dev_free(st->packed);
     st->pool_cap = 0;
     const size_t n = static_cast<size_t>(slots);
     EAHR_TRY(dev_alloc(&st->pairs, n));
     EAHR_TRY(dev_alloc(&st->keys, n));
     EAHR_TRY(dev_alloc(&st->keys_tmp, n));
-    EAHR_TRY(dev_alloc(&st->packed, n));
     st->pool_cap = slots;
     return EAHR_OK;
 }
@@ -857,7 +851,7 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
             pvs::launch_full_keys(v, st->vis, n, st->qrows, d_qidx, ng, keys, n, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[1], s));
-            const uint64_t* sorted = pvs::launch_segmented_sort(keys, tmp, d_cnt, d_sq, ng, n, s);
+            const uint64_t* sorted = pvs::launch_segmented_sort(keys, tmp, d_cnt, d_sq, ng, n, nullptr, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[2], s));
             for (int32_t i = 0; i < ng; ++i) {
@@ -1023,7 +1017,6 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     HIP_TRY(hipMemcpyAsync(st->scanq, st->h_scanq, nq * sizeof(ScanQ), hipMemcpyHostToDevice, s));
     int32_t* d_cert = st->counts;
     int32_t* d_fail = st->counts + nq;
-    int32_t* d_offs = st->counts + 2 * nq;
     int32_t* d_reads = st->counts + reads_counts_at(nq);
     int32_t* d_cbase = st->counts + 3 * nq + 2;
     int32_t* d_pcnt = st->counts + pair_counts_at(nq);
@@ -1113,8 +1106,8 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     }
     if (clamped)
         HIP_TRY(hipMemcpyAsync(d_cert, st->h_counts, nq * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    // the packed layout: query i's keys at h_offs[i] (the pack kernel's
-    // exclusive prefix of the same counts)
+    // the packed layout: query i's keys at h_offs[i] (the sort takes the same
+    // prefix of the same counts)
     const int32_t* h_cert = st->h_counts;
     const int32_t* h_fail = st->h_counts + nq;
     std::vector<int64_t> h_offs(static_cast<size_t>(nq) + 1, 0);
@@ -1122,19 +1115,17 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     const int64_t n_packed = h_offs[nq];
     EAHR_TRY(ensure_host_packed(st, n_packed));
     EAHR_TRY(mark(6));
-    uint64_t* sorted = pvs::launch_segmented_sort(st->keys, st->keys_tmp, d_cert, st->scanq, nq, max_cert, s);
-    pvs::launch_pack(sorted, d_cert, st->scanq, nq, max_cert, d_offs, st->packed, s);
+    // The last kernel writes the sorted keys, query after query, straight into
+    // the pinned copy (a copy from device memory moves them at the same rate
+    // and costs a launch).  They stay there (pending) until the next scan
+    // round, which appends them to the caches, while the ranks they hold are
+    // emitted straight from the copy.
+    pvs::launch_segmented_sort(st->keys, st->keys_tmp, d_cert, st->scanq, nq, max_cert, st->h_packed, s);
     EAHR_TRY(mark(5));
     HIP_TRY(hipGetLastError());
     if (prof)
         HIP_TRY(hipMemcpyAsync(st->h_counts + reads_counts_at(nq), d_reads,
                                static_cast<size_t>(pvs::kSub) * pvs::kCntStride * sizeof(int32_t),
-                               hipMemcpyDeviceToHost, s));
-    // The keys come back into the pinned copy; they stay there (pending)
-    // until the next scan round, which appends them to the caches, while the
-    // ranks they hold are emitted straight from the copy.
-    if (n_packed > 0)
-        HIP_TRY(hipMemcpyAsync(st->h_packed, st->packed, static_cast<size_t>(n_packed) * sizeof(uint64_t),
                                hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     tp[4] = clk::now();

@@ -114,7 +114,6 @@ struct ScanBuffers {
     uint4* pairs = nullptr;         // candidate pair records of a scan (pool)
     uint64_t* keys = nullptr;
     uint64_t* keys_tmp = nullptr;
-    uint64_t* packed = nullptr;
     pvs::ScanQ* h_scanq = nullptr;
     int32_t* h_counts = nullptr;
     uint64_t* h_packed = nullptr;
@@ -202,7 +201,6 @@ struct pvs_state {
     uint4* pairs = nullptr;
     uint64_t* keys = nullptr;
     uint64_t* keys_tmp = nullptr;
-    uint64_t* packed = nullptr;
     pvs::ScanPath path = pvs::ScanPath::Auto;
     bool spec_off = false;             // scans certify no further ahead than asked
     // test knob: first-attempt key regions and pool divided by this, so that

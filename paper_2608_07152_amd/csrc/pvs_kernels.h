@@ -8,7 +8,7 @@ namespace pvs {
 constexpr int kBlockRows = 64;     // rows per code block (one wavefront lane per row)
 constexpr int kChunk = 16;         // bytes of one code chunk (one 16-byte load per lane)
 constexpr int kMaxDim = 4096;      // 127^2 * 4096 < 2^31 and a_m < 1
-constexpr int kSortTile = 2048;    // keys sorted per workgroup in LDS
+constexpr int kSortTile = 2048;    // keys merged per workgroup
 constexpr int kMaxGemvQueries = 8; // queries per GEMV scan pass
 constexpr int kMaxMfmaQueries = 256;  // queries per MFMA scan pass (8 tiles of 32)
 // The candidate pool of a scan is split into kSub sub-regions, each with its
@@ -128,19 +128,20 @@ void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, in
                     int32_t* cert_cnt, int32_t* fail, int32_t* row_reads, int32_t fail_qi,
                     hipStream_t stream);
 
-// Sorts every query's candidate keys (cnt[b] keys from cand_off) ascending;
-// returns the buffer holding the result (keys or tmp).
 // Exhaustive float32 keys of every row of [0, n_rows) for ng queries (state
 // query indices qidx, device), query g's keys at keys + g * ld; invisible rows
 // get ~0.
 void launch_full_keys(const IndexView& ix, const uint64_t* vis, int64_t n_rows, const float* qrows,
                       const int32_t* qidx, int32_t ng, uint64_t* keys, int64_t ld,
                       hipStream_t stream);
+// Sorts every query's candidate keys (cnt[b] keys from cand_off) ascending;
+// returns the buffer holding the result: keys or tmp (each query's keys from
+// its cand_off), or, when given, packed, with the queries' keys one after
+// another.  packed may be pinned host memory: only the last kernel writes it,
+// and nothing reads it.
 uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt,
-                                const ScanQ* sq, int32_t nq, int64_t max_cnt, hipStream_t stream);
-
-void launch_pack(const uint64_t* keys, const int32_t* cert_cnt, const ScanQ* sq, int32_t nq,
-                 int64_t max_cnt, int32_t* offs, uint64_t* packed, hipStream_t stream);
+                                const ScanQ* sq, int32_t nq, int64_t max_cnt, uint64_t* packed,
+                                hipStream_t stream);
 
 void launch_intervals(const IndexView& ix, const int8_t* qcodes, const ScanQ* sq, float gamma,
                       const int64_t* rows, int64_t n, float* lo, float* hi, hipStream_t stream);

@@ -274,39 +274,169 @@ void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, in
 #undef PVS_RS
 }
 
+// Where query b's keys start when the queries' keys lie one after another:
+// the sum of the counts before it, taken by the whole workgroup.
+__device__ __forceinline__ int64_t packed_offset(const int32_t* __restrict__ cnt, int b) {
+    __shared__ int64_t part[16];
+    const int waves = static_cast<int>(blockDim.x >> 6), wave = static_cast<int>(threadIdx.x >> 6);
+    int64_t x = 0;
+    for (int i = threadIdx.x; i < b; i += blockDim.x) x += cnt[i];
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if ((threadIdx.x & 63) == 0) part[wave] = x;
+    __syncthreads();
+    x = 0;
+    for (int w = 0; w < waves; ++w) x += part[w];
+    return x;
+}
+
 // ------------------------------------------------------------------ sorting
-// Ascending sort of every tile of kSortTile keys of every query's region
-// (bitonic network in LDS; keys past the region's count are padded with ~0
-// and not written back).
-__global__ __launch_bounds__(256) void k_sort_tiles(uint64_t* __restrict__ keys,
-                                                    const int32_t* __restrict__ cnt,
-                                                    const ScanQ* __restrict__ sq) {
-    __shared__ uint64_t s[kSortTile];
+// Ascending sort of every tile of 512 WAVES keys of every query's region.
+// Keys past the region's count are padded with ~0 (no real key: a row id is
+// below 2^31) and not written back.
+//
+// A bitonic network over registers: thread t holds keys [8 t, 8 t + 8), so a
+// step of stride below 8 stays inside a thread, below 512 inside a wavefront
+// (lane exchanges), and only the strides between wavefronts go through LDS:
+// 3 such steps for four wavefronts and 6 for eight.  Every step runs
+// ascending: the first step of a merge compares mirrored positions.  Bound by
+// the vector instructions of one tile's chain of steps when there are few
+// tiles.  One tile of 2,048 keys takes 11.3 us; a network that kept every key
+// in LDS, with a barrier after each of its 66 steps, took 64 us.
+__device__ __forceinline__ void key_order(uint64_t& a, uint64_t& b) {
+    const bool sw = b < a;
+    const uint64_t x = sw ? b : a, y = sw ? a : b;
+    a = x;
+    b = y;
+}
+
+// The key of lane l ^ X of a wavefront.  X is a single bit below 64 or a full
+// mask 2^k - 1 (a mirrored step).  Inside 16 lanes these are data-parallel
+// moves (quad permutations, mirrored lanes, a rotation by 8); across rows of
+// 16 and halves of 32 the swap instructions give both sides' values.  The
+// LDS lane permutation in their place took 45 us instead of 37 for a tile of 8,192 keys
+// and sixteen wavefronts.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, 0xF, 0xF, false);
+    return (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
+}
+
+template <int X>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t x) {
+    static_assert(X == 1 || X == 2 || X == 3 || X == 4 || X == 7 || X == 8 || X == 15 || X == 16 || X == 31 ||
+                      X == 32 || X == 63, "a single bit or a full mask");
+    if constexpr (X == 1) return dpp64<0xB1>(x);
+    else if constexpr (X == 2) return dpp64<0x4E>(x);
+    else if constexpr (X == 3) return dpp64<0x1B>(x);
+    else if constexpr (X == 4) return dpp64<0x141>(dpp64<0x1B>(x));   // 7 ^ 3
+    else if constexpr (X == 7) return dpp64<0x141>(x);
+    else if constexpr (X == 8) return dpp64<0x128>(x);
+    else if constexpr (X == 15) return dpp64<0x140>(x);
+    else if constexpr (X == 31) return lane_xor<16>(lane_xor<15>(x));
+    else if constexpr (X == 63) return lane_xor<32>(lane_xor<31>(x));
+    else {
+        const uint32_t lo = static_cast<uint32_t>(x), hi = static_cast<uint32_t>(x >> 32);
+        const bool upper = (threadIdx.x & X) != 0;
+        uint32_t l, h;
+        if constexpr (X == 16) {
+            const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto c = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            l = upper ? a[0] : a[1];
+            h = upper ? c[0] : c[1];
+        } else {
+            const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto c = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            l = upper ? a[0] : a[1];
+            h = upper ? c[0] : c[1];
+        }
+        return (static_cast<uint64_t>(h) << 32) | l;
+    }
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_sort_tiles(const uint64_t* __restrict__ keys,
+                                                           uint64_t* __restrict__ dst, int packed,
+                                                           const int32_t* __restrict__ cnt,
+                                                           const ScanQ* __restrict__ sq) {
+    constexpr int PER = 8;
+    constexpr int T = 64 * WAVES * PER;
+    __shared__ uint64_t s[T];
+    const int tid = threadIdx.x;
     const int b = blockIdx.y;
     const int64_t n = cnt[b];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kSortTile;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * T;
     if (base >= n) return;
-    uint64_t* k = keys + sq[b].cand_off + base;
-    const int64_t m = min(static_cast<int64_t>(kSortTile), n - base);
-    for (int i = threadIdx.x; i < kSortTile; i += 256) s[i] = (i < m) ? k[i] : ~0ull;
-    __syncthreads();
-    for (int size = 2; size <= kSortTile; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < kSortTile; i += 256) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool asc = (i & size) == 0;
-                    const uint64_t a = s[i], c = s[j];
-                    if ((a > c) == asc) {
-                        s[i] = c;
-                        s[j] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
+    const int m = static_cast<int>(min(static_cast<int64_t>(T), n - base));
+    const uint64_t* k = keys + sq[b].cand_off + base;
+    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off) + base;
+    uint64_t v[PER];
+    // any assignment of the unsorted keys to threads will do: the coalesced one
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int at = i * 64 * WAVES + tid;
+        v[i] = at < m ? k[at] : ~0ull;
     }
-    for (int i = threadIdx.x; i < m; i += 256) k[i] = s[i];
+    // sizes 2, 4, 8: inside the thread
+    key_order(v[0], v[1]); key_order(v[2], v[3]); key_order(v[4], v[5]); key_order(v[6], v[7]);
+    key_order(v[0], v[3]); key_order(v[1], v[2]); key_order(v[4], v[7]); key_order(v[5], v[6]);
+    key_order(v[0], v[1]); key_order(v[2], v[3]); key_order(v[4], v[5]); key_order(v[6], v[7]);
+    auto half_clean = [&]() {   // strides 4, 2, 1
+        key_order(v[0], v[4]); key_order(v[1], v[5]); key_order(v[2], v[6]); key_order(v[3], v[7]);
+        key_order(v[0], v[2]); key_order(v[1], v[3]); key_order(v[4], v[6]); key_order(v[5], v[7]);
+        key_order(v[0], v[1]); key_order(v[2], v[3]); key_order(v[4], v[5]); key_order(v[6], v[7]);
+    };
+    key_order(v[0], v[7]); key_order(v[1], v[6]); key_order(v[2], v[5]); key_order(v[3], v[4]);
+    key_order(v[0], v[2]); key_order(v[1], v[3]); key_order(v[4], v[6]); key_order(v[5], v[7]);
+    key_order(v[0], v[1]); key_order(v[2], v[3]); key_order(v[4], v[5]); key_order(v[6], v[7]);
+    // this thread keeps the smaller keys of each pair when `low`
+    auto keep = [&](const uint64_t (&p)[PER], bool low) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = ((p[i] < v[i]) == low) ? p[i] : v[i];
+    };
+    auto exchange = [&](uint64_t (&p)[PER], int x, bool mirror) {   // p[i] = thread t ^ x's key
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) s[i * 64 * WAVES + tid] = v[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) p[i] = s[(mirror ? PER - 1 - i : i) * 64 * WAVES + (tid ^ x)];
+    };
+    // the merge of 2^LEVEL threads' keys: a mirrored step (thread
+    // t ^ (2^LEVEL - 1), register 7 - i), then strides 8 x: thread t ^ x
+    static_for(
+        [&](auto L_) {
+            constexpr int LEVEL = decltype(L_)::value + 1;
+            uint64_t p[PER];
+            if constexpr (LEVEL <= 6) {
+#pragma unroll
+                for (int i = 0; i < PER; ++i) p[i] = lane_xor<(1 << LEVEL) - 1>(v[PER - 1 - i]);
+            } else {
+                exchange(p, (1 << LEVEL) - 1, true);
+            }
+            keep(p, (tid & (1 << (LEVEL - 1))) == 0);
+            static_for(
+                [&](auto J_) {
+                    constexpr int X = 1 << (LEVEL - 2 - decltype(J_)::value);
+                    uint64_t r[PER];
+                    if constexpr (X < 64) {
+#pragma unroll
+                        for (int i = 0; i < PER; ++i) r[i] = lane_xor<X>(v[i]);
+                    } else {
+                        exchange(r, X, false);
+                    }
+                    keep(r, (tid & X) == 0);
+                },
+                std::make_integer_sequence<int, LEVEL - 1>{});
+            half_clean();
+        },
+        std::make_integer_sequence<int, WAVES == 1 ? 6 : WAVES == 4 ? 8 : 9>{});
+    // through LDS once more, so that neighbouring lanes write neighbouring keys
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s[tid * PER + i] = v[i];
+    __syncthreads();
+    for (int i = tid; i < m; i += 64 * WAVES) d[i] = s[i];
 }
 
 // One merge level: runs of length `run` (a multiple of kSortTile) are merged
@@ -317,7 +447,7 @@ __global__ __launch_bounds__(256) void k_sort_tiles(uint64_t* __restrict__ keys,
 // unique inside a query), those are staged in LDS, and each thread merges
 // eight consecutive outputs after a search of its own diagonal there.
 __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
-                                               uint64_t* __restrict__ dst,
+                                               uint64_t* __restrict__ dst, int packed,
                                                const int32_t* __restrict__ cnt,
                                                const ScanQ* __restrict__ sq, int64_t run) {
     constexpr int T = kSortTile;
@@ -332,7 +462,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
     if (o0 >= n) return;
     const int64_t o1 = min(o0 + T, n);
     const uint64_t* s = src + sq[b].cand_off;
-    uint64_t* d = dst + sq[b].cand_off;
+    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off);
     const int64_t start = (o0 / (2 * run)) * (2 * run);
     const int64_t mid = min(start + run, n);
     const int64_t end = min(start + 2 * run, n);
@@ -387,56 +517,37 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
     for (int i = threadIdx.x; i < na + nb; i += 256) d[o0 + i] = out[i];
 }
 
+// Tiles of 512 keys by one wavefront, 2,048 by four, 4,096 by eight: the
+// smallest that holds the longest list, so that short lists need no merge
+// (one tile of 512 takes 7.3 us, of 2,048 11.3 us; a merge level of a few
+// thousand keys takes 8 us and its launch).  Longer lists start from 4,096:
+// a tile of 8,192 keys took 37 us, more than two of its halves and a merge.
 uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt,
-                                const ScanQ* sq, int32_t nq, int64_t max_cnt, hipStream_t stream) {
-    if (nq <= 0 || max_cnt <= 0) return keys;
-    const int64_t tiles = (max_cnt + kSortTile - 1) / kSortTile;
-    hipLaunchKernelGGL(k_sort_tiles, dim3(static_cast<uint32_t>(tiles), nq), dim3(256), 0, stream,
-                       keys, cnt, sq);
-    uint64_t* a = keys;
+                                const ScanQ* sq, int32_t nq, int64_t max_cnt, uint64_t* packed,
+                                hipStream_t stream) {
+    if (nq <= 0 || max_cnt <= 0) return packed ? packed : keys;
+    const int64_t tile = max_cnt <= 512 ? 512 : max_cnt <= 2048 ? 2048 : 4096;
+    const dim3 grid(static_cast<uint32_t>((max_cnt + tile - 1) / tile), nq);
+    uint64_t* a = (packed && tile >= max_cnt) ? packed : keys;
+    const int direct = a == packed;
+    if (tile == 512)
+        hipLaunchKernelGGL(k_sort_tiles<1>, grid, dim3(64), 0, stream, keys, a, direct, cnt, sq);
+    else if (tile == 2048)
+        hipLaunchKernelGGL(k_sort_tiles<4>, grid, dim3(256), 0, stream, keys, a, direct, cnt, sq);
+    else
+        hipLaunchKernelGGL(k_sort_tiles<8>, grid, dim3(512), 0, stream, keys, a, direct, cnt, sq);
     uint64_t* b = tmp;
-    for (int64_t run = kSortTile; run < max_cnt; run *= 2) {
+    for (int64_t run = tile; run < max_cnt; run *= 2) {
         const int64_t g = (max_cnt + kSortTile - 1) / kSortTile;
+        const bool last = 2 * run >= max_cnt;
+        if (last && packed) b = packed;
         hipLaunchKernelGGL(k_merge, dim3(static_cast<uint32_t>(g), nq), dim3(256), 0, stream, a, b,
-                           cnt, sq, run);
+                           last && packed ? 1 : 0, cnt, sq, run);
         uint64_t* t = a;
         a = b;
         b = t;
     }
     return a;
-}
-
-// ----------------------------------------------------------------- packing
-__global__ __launch_bounds__(64) void k_offsets(const int32_t* __restrict__ cert, int32_t nq,
-                                                int32_t* __restrict__ offs) {
-    if (threadIdx.x == 0) {
-        int32_t acc = 0;
-        for (int b = 0; b < nq; ++b) {
-            offs[b] = acc;
-            acc += cert[b];
-        }
-        offs[nq] = acc;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_pack(const uint64_t* __restrict__ keys,
-                                              const int32_t* __restrict__ cert,
-                                              const int32_t* __restrict__ offs,
-                                              const ScanQ* __restrict__ sq,
-                                              uint64_t* __restrict__ packed) {
-    const int b = blockIdx.y;
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < cert[b]) packed[offs[b] + i] = keys[sq[b].cand_off + i];
-}
-
-void launch_pack(const uint64_t* keys, const int32_t* cert_cnt, const ScanQ* sq, int32_t nq,
-                 int64_t max_cnt, int32_t* offs, uint64_t* packed, hipStream_t stream) {
-    if (nq <= 0) return;
-    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(64), 0, stream, cert_cnt, nq, offs);
-    if (max_cnt <= 0) return;
-    const int64_t g = (max_cnt + 255) / 256;
-    hipLaunchKernelGGL(k_pack, dim3(static_cast<uint32_t>(g), nq), dim3(256), 0, stream, keys,
-                       cert_cnt, offs, sq, packed);
 }
 
 }  // namespace pvs
