@@ -378,8 +378,7 @@ pvs_state::~pvs_state() {
 void pvs_state::release_scan_buffers() {
     dev_free(scanq);
     dev_free(counts);
-    dev_free(sample_lo);
-    dev_free(sample_hi);
+    dev_free(sample);
     dev_free(qfrag);
     dev_free(pairs);
     dev_free(keys);
@@ -398,7 +397,7 @@ void pvs_state::release_scan_buffers() {
 
 // Move the scan buffers between a state and an index's spare slot.
 #define PVS_BUFFER_FIELDS(X)                                                                 \
-    X(buf_nq) X(buf_sample) X(scanq) X(counts) X(sample_lo) X(sample_hi) X(qfrag) X(pool_cap) \
+    X(buf_nq) X(buf_sample) X(scanq) X(counts) X(sample) X(qfrag) X(pool_cap) \
     X(pairs) X(keys) X(keys_tmp) X(h_scanq) X(h_counts)    \
     X(h_packed) X(h_packed_cap)
 
@@ -434,8 +433,7 @@ static void donate_buffers(pvs_state* st, ScanBuffers& b) {
     st->h_packed_cap = 0;
     st->scanq = nullptr;
     st->counts = nullptr;
-    st->sample_lo = nullptr;
-    st->sample_hi = nullptr;
+    st->sample = nullptr;
     st->qfrag = nullptr;
     st->pairs = nullptr;
     st->keys = nullptr;
@@ -448,8 +446,7 @@ static void donate_buffers(pvs_state* st, ScanBuffers& b) {
 static void free_buffers(ScanBuffers& b) {
     dev_free(b.scanq);
     dev_free(b.counts);
-    dev_free(b.sample_lo);
-    dev_free(b.sample_hi);
+    dev_free(b.sample);
     dev_free(b.qfrag);
     dev_free(b.pairs);
     dev_free(b.keys);
@@ -485,8 +482,7 @@ static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
     HIP_TRY(hipStreamSynchronize(st->ix->stream));
     dev_free(st->scanq);
     dev_free(st->counts);
-    dev_free(st->sample_lo);
-    dev_free(st->sample_hi);
+    dev_free(st->sample);
     dev_free(st->qfrag);
     if (st->h_scanq) (void)hipHostFree(st->h_scanq);
     if (st->h_counts) (void)hipHostFree(st->h_counts);
@@ -494,8 +490,7 @@ static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
     st->h_counts = nullptr;
     EAHR_TRY(dev_alloc(&st->scanq, nq));
     EAHR_TRY(dev_alloc(&st->counts, all_counts(nq)));
-    EAHR_TRY(dev_alloc(&st->sample_lo, static_cast<size_t>(nq) * sample_ld));
-    EAHR_TRY(dev_alloc(&st->sample_hi, static_cast<size_t>(nq) * sample_ld));
+    EAHR_TRY(dev_alloc(&st->sample, static_cast<size_t>(nq) * sample_ld));
     int8_t* f;
     EAHR_TRY(dev_alloc(&f, static_cast<size_t>(st->ix->dp / 32) * 8 * 64 * 16));
     st->qfrag = f;
@@ -922,8 +917,7 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         todo.clear();
         return EAHR_OK;
     }
-    int64_t stride = 1;
-    while (nblocks / (stride * 2) >= pvs::kSampleBlocks) stride *= 2;
+    const int64_t stride = std::max<int64_t>(1, nblocks / pvs::kSampleBlocks);
     const int64_t nsb = (nblocks + stride - 1) / stride;
     const int64_t sample_ld = nsb * 64;
     const double frac = static_cast<double>(nsb) / static_cast<double>(nblocks);
@@ -970,13 +964,14 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     // 1. threshold and candidate estimate from the sampled blocks
     HIP_TRY(hipMemcpyAsync(st->scanq, st->h_scanq, nq * sizeof(ScanQ), hipMemcpyHostToDevice, s));
     pvs::ScanOut so;
-    so.sample_lo = st->sample_lo;
-    so.sample_hi = st->sample_hi;
+    so.sample = st->sample;
+    so.sample_mid = stride > 1 ? 1 : 0;
+    so.norm_sum = ix->nv_max + ix->nev_max;
     so.sample_ld = sample_ld;
     so.sample_stride = stride;
     EAHR_TRY(mark(0));
     scan(true, so, nq);
-    pvs::launch_select(st->sample_lo, st->sample_hi, sample_ld, sample_ld, stride > 1, st->scanq, nq, s);
+    pvs::launch_select(st->sample, sample_ld, sample_ld, so.norm_sum, st->scanq, nq, s);
     EAHR_TRY(mark(1));
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(st->h_scanq, st->scanq, nq * sizeof(ScanQ), hipMemcpyDeviceToHost, s));

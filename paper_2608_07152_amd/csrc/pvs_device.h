@@ -124,6 +124,30 @@ __device__ __forceinline__ float scaled_threshold(float thr, float sq) {
     return (r > -INFINITY && r < INFINITY) ? r : -INFINITY;
 }
 
+// A sampled pair is kept as two half floats: the value tau is selected from
+// (lower bound or midpoint) in the low half, the upper bound in the high one,
+// both times a power of two of the query that puts the largest score bound of
+// the index just below 2^15, and rounded towards zero.  So the halves order
+// like the values, to 2^-10 relative (the guard term alone makes an interval
+// wider than that), and a value is never below its half when that is >= 0.
+// Pairs that are not eligible hold -inf twice.
+constexpr uint32_t kSampleNone = 0xfc00fc00u;
+
+template <typename QF>
+__device__ __forceinline__ int sample_exp(const QF& Q, float norm_sum) {
+    const float L = Q.nqh * norm_sum + Q.wmax;   // at least wmax > 0
+    return static_cast<int>(__float_as_uint(L) >> 23) - 127;
+}
+__device__ __forceinline__ float pow2f(int e) { return __uint_as_float(static_cast<uint32_t>(127 + e) << 23); }
+
+__device__ __forceinline__ uint32_t sample_pack(float lo, float hi, bool midpoint, float scale) {
+    const float v = midpoint ? 0.5f * lo + 0.5f * hi : lo;
+    const auto h = __builtin_amdgcn_cvt_pkrtz(v * scale, hi * scale);
+    uint32_t r;
+    __builtin_memcpy(&r, &h, 4);
+    return r;
+}
+
 // Sum of the 16 lanes of every row of the wavefront as a pairwise tree:
 // partners j ^ 1 and j ^ 2 (quad permutations), then the lane mirrored
 // within 8 and within 16 lanes, which after the earlier steps hold the same

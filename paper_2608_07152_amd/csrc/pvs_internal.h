@@ -15,8 +15,8 @@
 using KeyCache = std::vector<uint64_t, ::eahr::NoInit<uint64_t>>;
 
 namespace pvs {
-// Threshold estimation samples every stride-th code block, with the stride
-// the largest power of two that keeps at least this many blocks sampled.
+// Threshold estimation samples every stride-th code block, with the largest
+// stride that keeps at least this many blocks sampled.
 // With stride 1 tau is the target-th largest lower bound, so at least the
 // target is certified.  With a larger stride tau is taken from the sampled
 // interval midpoints (close to the scores, so the rows certified, s >= tau,
@@ -107,8 +107,7 @@ struct ScanBuffers {
     int64_t buf_sample = 0;
     pvs::ScanQ* scanq = nullptr;
     int32_t* counts = nullptr;
-    float* sample_lo = nullptr;
-    float* sample_hi = nullptr;
+    uint32_t* sample = nullptr;
     void* qfrag = nullptr;
     int64_t pool_cap = 0;
     uint4* pairs = nullptr;         // candidate pair records of a scan (pool)
@@ -193,8 +192,7 @@ struct pvs_state {
     int64_t buf_sample = 0;
     pvs::ScanQ* scanq = nullptr;
     int32_t* counts = nullptr;
-    float* sample_lo = nullptr;
-    float* sample_hi = nullptr;
+    uint32_t* sample = nullptr;
     void* qfrag = nullptr;             // query codes in MFMA operand order
     // candidate pool (pool_cap slots) split into per-query regions per scan
     int64_t pool_cap = 0;

@@ -27,7 +27,7 @@ struct ScanQ {
     float s_cert;      // score of the last certified rank (valid if has_cert)
     int32_t id_cert;   // its row id
     int32_t has_cert;
-    int32_t k;         // rank of tau among sampled lower bounds (select pass)
+    int32_t k;         // rank of tau among the sampled values (select pass)
     float sq;          // s_q
     float nq;          // ||q||_2 rounded up
     float nqh;         // ||q_hat||_2 rounded up
@@ -60,9 +60,9 @@ void launch_quantize(const float* src, int64_t nrows, int32_t d, int64_t src_str
 // Largest |x| of count floats into flags[3] (float bits), non-finite into flags[0].
 void launch_maxabs(const float* src, int64_t count, uint32_t* flags, hipStream_t stream);
 
-// Outputs of a scan pass.  Sample pass: lower and upper bounds of every
-// (query, row) pair of the sampled blocks, row-major [query][sample_ld],
-// -inf / -inf for ineligible rows.  Main pass: every candidate pair (hi >= tau)
+// Outputs of a scan pass.  Sample pass: two half floats (sample_pack) of every
+// (query, row) pair of the sampled blocks, row-major [query][sample_ld].
+// Main pass: every candidate pair (hi >= tau)
 // becomes one record (row, index of the query in the scan, exact integer dot
 // product, 0).  A wavefront reserves all records of its block (or of its
 // block and half of the query tiles, in the wide MFMA kernel) with one atomic
@@ -73,10 +73,11 @@ void launch_maxabs(const float* src, int64_t count, uint32_t* flags, hipStream_t
 // one row next to each other, so rescoring reads the row once for all of
 // them.
 struct ScanOut {
-    float* sample_lo = nullptr;
-    float* sample_hi = nullptr;
+    uint32_t* sample = nullptr;
     int64_t sample_ld = 0;
     int64_t sample_stride = 1;   // sampled blocks are multiples of this
+    int32_t sample_mid = 0;      // tau is selected from midpoints, not lower bounds
+    float norm_sum = 0.0f;       // largest ||v|| plus largest ||e_v|| of the index
     uint4* pairs = nullptr;
     int64_t pair_sub = 0;        // records per sub-region
     int32_t* pair_cnt = nullptr;
@@ -101,11 +102,11 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const ScanOut& o, void* frag, hipStream_t stream);
 int mfma_tiles_for(int32_t nq);
 
-// tau = k-th largest finite sampled lower bound (or, with midpoint, sampled
-// interval midpoint); sample_hits = sampled pairs with hi >= tau (both
-// written into sq).
-void launch_select(const float* sample_lo, const float* sample_hi, int64_t n, int64_t ld,
-                   bool midpoint, ScanQ* sq, int32_t nq, hipStream_t stream);
+// tau = the k-th largest selection value of each query's sample, rounded down
+// to a half float (-inf when fewer than k pairs are eligible); sample_hits =
+// sampled pairs with hi >= tau (both written into sq).
+void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum, ScanQ* sq, int32_t nq,
+                   hipStream_t stream);
 
 // Rescoring reads the kept records of every sub-region of the pool (at most
 // pair_sub each, in chunks of kRescoreChunk; chunks = rescore_chunks of the

@@ -69,9 +69,9 @@ __global__ __launch_bounds__(256) void k_scan_gemv(
         pair_interval(Q, sv, nv, nev, acc[b], gamma, lo, hi);
         const bool elig = visible && (!Q.has_cert || lo <= Q.s_cert);
         if (SAMPLE) {
-            const int64_t i = b * o.sample_ld + w * 64 + lane;
-            o.sample_lo[i] = elig ? lo : -INFINITY;
-            o.sample_hi[i] = elig ? hi : -INFINITY;
+            const float scale = pow2f(14 - sample_exp(Q, o.norm_sum));
+            o.sample[b * o.sample_ld + w * 64 + lane] =
+                elig ? sample_pack(lo, hi, o.sample_mid != 0, scale) : kSampleNone;
         } else if (elig && hi >= Q.tau) {
             take |= 1u << b;
         }
@@ -127,8 +127,7 @@ static void gemv_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
 
 static ScanOut shift_out(const ScanOut& o, int32_t q0) {
     ScanOut s = o;
-    if (s.sample_lo) s.sample_lo += q0 * o.sample_ld;
-    if (s.sample_hi) s.sample_hi += q0 * o.sample_ld;
+    if (s.sample) s.sample += q0 * o.sample_ld;
     s.qbase = o.qbase + q0;
     return s;
 }
@@ -347,8 +346,11 @@ __global__ __launch_bounds__(256) void k_scan_mfma(
         }
     const uint4* A = codes + blk * nchunk * 64 + (lane >> 5) * 64 + (lane & 31);
     const int nsteps = nchunk >> 1;
+    // a sample pass has few blocks: its halves are workgroups of their own
+    const int ub = SAMPLE ? static_cast<int>(blockIdx.y) * NQS : 0;
+    const int ue = SAMPLE ? ub + NQS : NQT;
 #pragma unroll 1
-    for (int u0 = 0; u0 < NQT; u0 += NQS) {
+    for (int u0 = ub; u0 < ue; u0 += NQS) {
     v16i acc[2][NQS];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -377,18 +379,25 @@ __global__ __launch_bounds__(256) void k_scan_mfma(
         const ScanQ Q = sq[valid ? b : 0];
         mask[uu] = 0;
         if (SAMPLE) {
+            // a lane's four consecutive rows go out in one store
             if (!valid) continue;
+            const float scale = pow2f(14 - sample_exp(Q, o.norm_sum));
+            uint32_t* dst = o.sample + b * o.sample_ld + w * 64 + 4 * (lane >> 5);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int rib = 32 * t + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    float lo, hi;
-                    pair_interval(Q, svr[t][r], vnr[t][r], enr[t][r], acc[t][uu][r], gamma, lo, hi);
-                    const bool elig = ((vbits >> rib) & 1ull) && (!Q.has_cert || lo <= Q.s_cert);
-                    const int64_t i = b * o.sample_ld + w * 64 + rib;
-                    o.sample_lo[i] = elig ? lo : -INFINITY;
-                    o.sample_hi[i] = elig ? hi : -INFINITY;
+                for (int g = 0; g < 4; ++g) {
+                    uint32_t x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = 4 * g + e;
+                        const int rib = 32 * t + 8 * g + 4 * (lane >> 5) + e;
+                        float lo, hi;
+                        pair_interval(Q, svr[t][r], vnr[t][r], enr[t][r], acc[t][uu][r], gamma, lo, hi);
+                        const bool elig = ((vbits >> rib) & 1ull) && (!Q.has_cert || lo <= Q.s_cert);
+                        x[e] = elig ? sample_pack(lo, hi, o.sample_mid != 0, scale) : kSampleNone;
+                    }
+                    *reinterpret_cast<uint4*>(dst + 32 * t + 8 * g) = make_uint4(x[0], x[1], x[2], x[3]);
                 }
             }
             continue;
@@ -660,7 +669,7 @@ __device__ __forceinline__ float max32(float v) {
                  __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16)));
 }
 
-template <int NQT, int NG, int NS, int P, int W>
+template <int NQT, int NG, int NS, int P, int W, bool SAMPLE>
 __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     const uint4* __restrict__ codes, const float* __restrict__ scale,
     const float* __restrict__ vnorm, const float* __restrict__ enorm,
@@ -702,16 +711,17 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     }
     __syncthreads();
     float* meta = s_meta + wave * 96;
-    const int64_t nhalves = 2 * nblocks;
+    const int64_t nhalves = 2 * (SAMPLE ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks);
+    auto block_of = [&](int64_t x) { return SAMPLE ? (x >> 1) * o.sample_stride : x >> 1; };
     const int64_t stride = static_cast<int64_t>(gridDim.x) * W;
     int64_t hb = static_cast<int64_t>(blockIdx.x) * W + wave;
     const __amdgpu_buffer_rsrc_t qrs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<v4i*>(qfrag), 0, 0x7fffffff, 0x00020000);
     const int32_t qf_off = lane * 16;
     const int32_t code_off = ((lane >> 5) * 64 + (lane & 31)) * 16;
-    auto half_rsrc = [&](int64_t x) {   // codes of half-block x (32 rows of block x / 2)
+    auto half_rsrc = [&](int64_t x) {   // codes of half-block x (32 rows of block block_of(x))
         return __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint4*>(codes + (x >> 1) * nchunk * 64 + 32 * (x & 1)), 0, 0x7fffffff, 0x00020000);
+            const_cast<uint4*>(codes + block_of(x) * nchunk * 64 + 32 * (x & 1)), 0, 0x7fffffff, 0x00020000);
     };
     v4i a[P];                     // ring: slot s % P holds step s
     v4i g[2][NG > 0 ? NG : 1];    // global tiles, two steps ahead
@@ -726,11 +736,11 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     float sv0 = 0.0f, nv0 = 0.0f, nev0 = 0.0f;
     uint32_t vbits = 0;
     auto load_meta = [&](int64_t x) {
-        const int64_t row = (x >> 1) * 64 + 32 * (x & 1) + (lane & 31);
+        const int64_t row = block_of(x) * 64 + 32 * (x & 1) + (lane & 31);
         sv0 = scale[row];
         nv0 = vnorm[row];
         nev0 = enorm[row];
-        vbits = static_cast<uint32_t>(vis[x >> 1] >> (32 * (x & 1)));
+        vbits = static_cast<uint32_t>(vis[block_of(x)] >> (32 * (x & 1)));
     };
     if (hb < nhalves) {
         load_meta(hb);
@@ -749,6 +759,7 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
         const __amdgpu_buffer_rsrc_t rs_nxt = half_rsrc(more ? nxt : hb);
         // this half-block's metadata (invisible rows carry a NaN scale)
         const bool visible = (vbits >> (lane & 31)) & 1u;
+        [[maybe_unused]] const uint32_t vcur = vbits;
         if (lane < 32) {
             meta[lane] = visible ? sv0 : __builtin_nanf("");
             meta[32 + lane] = nv0;
@@ -789,6 +800,42 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
             __builtin_amdgcn_sched_barrier(0);   // keep each step's loads in its step
         }
         if (more) load_meta(nxt);
+        if constexpr (SAMPLE) {
+            // every pair's interval, four consecutive rows of a query in one
+            // 16-byte store (a lane's accumulators 4 g .. 4 g + 3).  256
+            // queries of d = 768: 113 us for 2,048 blocks; one wavefront per
+            // block with two 4-byte stores a pair took 313 us.
+            __builtin_amdgcn_wave_barrier();
+            const int h4 = 4 * (lane >> 5);
+            uint32_t* srow = o.sample + (hb >> 1) * 64 + 32 * (hb & 1) + h4;
+#pragma unroll
+            for (int uu = 0; uu < NQT; ++uu) {
+                const int b = 32 * uu + (lane & 31);
+                const QFields f = s_qf[b];
+                ScanQ Q{};
+                Q.sq = f.sq;
+                Q.nq = f.nq;
+                Q.nqh = f.nqh;
+                Q.neq = f.neq;
+                const float scl = pow2f(14 - sample_exp(f, o.norm_sum));
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    uint32_t x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int rih = 8 * g4 + h4 + e;
+                        float lo, hi;
+                        pair_interval(Q, meta[rih], meta[32 + rih], meta[64 + rih], acc[uu][4 * g4 + e], gamma, lo, hi);
+                        const bool elig = ((vcur >> rih) & 1u) && (!f.has_cert || lo <= f.s_cert);
+                        x[e] = elig ? sample_pack(lo, hi, o.sample_mid != 0, scl) : kSampleNone;
+                    }
+                    if (b < nq)
+                        *reinterpret_cast<uint4*>(srow + b * o.sample_ld + 8 * g4) = make_uint4(x[0], x[1], x[2], x[3]);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            continue;
+        }
         // Epilogue.  Pre-test of every pair, one compare per accumulator:
         // s_v * dot >= thq, thq from the half-block's largest norms with a
         // margin for the rounding of both products (invisible rows carry a
@@ -895,6 +942,7 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
         }
         if (fill) flush(fill);
     }
+    if constexpr (SAMPLE) return;
     __syncthreads();
     for (int b = tid; b < nq && b < NQT * 32; b += 64 * W)
         if (s_evals[b]) atomicAdd(&o.q_evals[(blockIdx.x & (kSub - 1)) * o.q_ld + o.qbase + b], s_evals[b]);
@@ -915,7 +963,7 @@ static int cu_count() {
 // for them); false when the index has another step count or the kernel
 // cannot get its LDS.  EAHR_MFMA_KERNEL=wide (testing) keeps the older
 // kernel.
-template <int NQT, int NG, int NS, int P, int W>
+template <int NQT, int NG, int NS, int P, int W, bool SAMPLE>
 static bool r1_launch(const IndexView& ix, const uint64_t* vis, int64_t nblocks, const v4i* qfrag,
                       const ScanQ* sq, int32_t nq, float gamma, const ScanOut& o, hipStream_t stream) {
     if (ix.nchunk / 2 != NS) return false;
@@ -926,15 +974,16 @@ static bool r1_launch(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                            W * 2 * (NQT <= 4 ? 64 * (NQT + 1) : 64) * sizeof(int32_t);
     static std::atomic<int> ready{0};   // 1: LDS attribute set, -1: refused
     if (ready.load() == 0) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scan_mfma_r1<NQT, NG, NS, P, W>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_scan_mfma_r1<NQT, NG, NS, P, W, SAMPLE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         ready.store(e == hipSuccess ? 1 : -1);
         if (e != hipSuccess) (void)hipGetLastError();
     }
     if (ready.load() < 0) return false;
-    const int64_t groups = (2 * nblocks + W - 1) / W;
+    const int64_t halves = 2 * (SAMPLE ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks);
+    const int64_t groups = (halves + W - 1) / W;
     const uint32_t g = static_cast<uint32_t>(std::min<int64_t>(groups, cu_count()));
-    hipLaunchKernelGGL((k_scan_mfma_r1<NQT, NG, NS, P, W>), dim3(g), dim3(64 * W), lds, stream, ix.codes, ix.scale,
+    hipLaunchKernelGGL((k_scan_mfma_r1<NQT, NG, NS, P, W, SAMPLE>), dim3(g), dim3(64 * W), lds, stream, ix.codes, ix.scale,
                        ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qfrag, sq, nq, gamma, o);
     return true;
 }
@@ -945,19 +994,20 @@ static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       hipStream_t stream) {
     const int64_t waves = sample ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks;
     const uint32_t grid = static_cast<uint32_t>((waves + 3) / 4);
-    if constexpr (NQT == 8) {
-        // 256 queries, d = 768: six tiles in LDS, two from L2; d = 384: all in LDS
-        if (!sample && (r1_launch<8, 2, 24, 6, 8>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
-                        r1_launch<8, 0, 12, 6, 8>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream)))
-            return;
-    }
-    if constexpr (NQT == 4) {
-        if (!sample && (r1_launch<4, 0, 24, 8, 12>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
-                        r1_launch<4, 0, 12, 6, 12>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream)))
-            return;
-    }
+    auto r1 = [&](auto sample_c) {
+        constexpr bool S = decltype(sample_c)::value;
+        if constexpr (NQT == 8)   // 256 queries, d = 768: six tiles in LDS, two from L2; d = 384: all in LDS
+            return r1_launch<8, 2, 24, 6, 8, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
+                   r1_launch<8, 0, 12, 6, 8, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream);
+        else if constexpr (NQT == 4)
+            return r1_launch<4, 0, 24, 8, 12, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
+                   r1_launch<4, 0, 12, 6, 12, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream);
+        else
+            return false;
+    };
+    if (sample ? r1(std::true_type{}) : r1(std::false_type{})) return;
     if (sample) {
-        hipLaunchKernelGGL((k_scan_mfma<NQT, true>), dim3(grid), dim3(256), 0, stream, ix.codes,
+        hipLaunchKernelGGL((k_scan_mfma<NQT, true>), dim3(grid, NQT > 4 ? NQT / 4 : 1), dim3(256), 0, stream, ix.codes,
                            ix.scale, ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qfrag, sq, nq,
                            gamma, o);
     } else if (NQT >= 4) {
@@ -1026,161 +1076,150 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
 }
 
 // ------------------------------------------------------------ threshold
-// One workgroup per query: tau = the k-th largest finite value among the
-// sampled lower bounds (midpoint == 0) or the sampled interval midpoints
-// (lo + hi) / 2 (midpoint == 1), by radix select over order-preserving keys,
-// 8 bits per pass below the leading bits that every key shares; -inf when
-// fewer than k are finite.  Then sample_hits = sampled pairs with hi >= tau.
-__device__ __forceinline__ float select_value(const float* x, const float* y, int64_t i, int midpoint) {
-    const float lo = x[i];
-    return (midpoint && lo != -INFINITY) ? 0.5f * lo + 0.5f * y[i] : lo;
+// tau = the k-th largest selection value of a query's sample, to the half
+// float it is kept as, and sample_hits = sampled pairs with hi >= tau.
+//
+// One pass over the sample counts both halves of every pair in two LDS
+// histograms, one bin per half float, over a window of 8,192 of them: eight
+// octaves below the largest score bound, which hold the k-th value unless it
+// is below 1/256 of that bound (then the next windows down follow, each with
+// its own pass).  A suffix sum finds the bin.  One workgroup per query, bound
+// by the latency of its loads: 8.8M x 768 (137K samples a query), 28 us for
+// one query, 33 us for 256; the earlier kernel, up to six radix passes over
+// two floats a pair, took 120 and 247 us.  Up to sixteen workgroups per query
+// that added their bins to a global histogram took 67 to 150 us: the atomics
+// cost more than the pass they split.
+constexpr int kBins = 8192;
+constexpr int kSelTop = 0xf800;   // order of the half float 2^15, above every kept value
+
+__device__ __forceinline__ int half_order(uint32_t h) {
+    return static_cast<int>((h & 0x8000u) ? (~h & 0xffffu) : (h | 0x8000u));
 }
 
-// Calls f(value) for every value of a query's sample (-inf: not finite),
-// reading 16 bytes per lane and four of them at a time: one workgroup per
-// query cannot hide the latency of 4-byte loads (a single request's select
-// ran at about 30 GB/s).  Rows of the sample start 16-byte aligned (they hold
-// whole 64-row blocks); a tail of n % 4 values, or a sample that is not
-// aligned, is read one value at a time.
-template <typename F>
-__device__ __forceinline__ void for_values(const float* x, const float* y, int64_t n, int midpoint, F&& f) {
-    constexpr int U = 4;
-    const float4* x4 = reinterpret_cast<const float4*>(x);
-    const float4* y4 = reinterpret_cast<const float4*>(y);
-    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y)) & 15u) == 0;
-    const int64_t n4 = aligned ? n >> 2 : 0;
-    for (int64_t i0 = threadIdx.x; i0 < n4; i0 += static_cast<int64_t>(blockDim.x) * U) {
-        float4 a[U], c[U];
+__global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sample, int64_t n,
+                                                 int64_t ld, float norm_sum, ScanQ* __restrict__ sq) {
+    __shared__ uint32_t bins[2][kBins];
+    __shared__ uint32_t s_part[2][16];
+    __shared__ uint32_t s_elig, s_bin, s_found;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t* x = sample + b * ld;
+    const ScanQ Q = sq[b];
+    const uint32_t k = static_cast<uint32_t>(Q.k);
+    uint32_t above[2] = {0u, 0u};   // values and upper bounds over the windows passed
+    uint32_t total = 0;
+    if (tid == 0) s_elig = 0;
+    for (int win = 0;; ++win) {
+        const int top = kSelTop - win * kBins, base = top - kBins;
+        for (int i = tid; i < 2 * kBins; i += 1024) (&bins[0][0])[i] = 0u;
+        __syncthreads();
+        const int64_t n4 = n >> 2;
+        const uint4* x4 = reinterpret_cast<const uint4*>(x);   // whole 64-row blocks: 16-byte aligned
+        uint32_t elig = 0;
+        for (int64_t i = tid; i < n4; i += 4096) {
+            uint4 v[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = i0 + static_cast<int64_t>(u) * blockDim.x;
-            a[u] = i < n4 ? x4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            c[u] = (midpoint && i < n4) ? y4[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
+            for (int u = 0; u < 4; ++u)
+                v[u] = i + 1024 * u < n4 ? x4[i + 1024 * u]
+                                         : make_uint4(kSampleNone, kSampleNone, kSampleNone, kSampleNone);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float lo[4] = {a[u].x, a[u].y, a[u].z, a[u].w};
-            const float hi[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) f((midpoint && lo[e] != -INFINITY) ? 0.5f * lo[e] + 0.5f * hi[e] : lo[e]);
-        }
-    }
-    for (int64_t i = 4 * n4 + threadIdx.x; i < n; i += blockDim.x) f(select_value(x, y, i, midpoint));
-}
-
-__global__ __launch_bounds__(1024) void k_select(const float* __restrict__ sample_lo,
-                                                 const float* __restrict__ sample_hi, int64_t n,
-                                                 int64_t ld, int midpoint, ScanQ* __restrict__ sq) {
-    // 32 copies of the digit histogram, lane l counting into copy l % 32: the
-    // keys of one query cluster in a few digits, and updates of one address
-    // from many lanes would be applied one at a time (stride 257 puts a
-    // digit's copies in different banks)
-    constexpr int kCopies = 32, kStride = 257;
-    __shared__ uint32_t hist[kCopies * kStride];
-    __shared__ uint32_t s_digit;
-    __shared__ uint32_t s_rest;
-    __shared__ uint32_t s_total;
-    __shared__ uint32_t s_hits;
-    __shared__ uint32_t s_kmin;
-    __shared__ uint32_t s_kmax;
-    __shared__ float s_tau;
-    const int b = blockIdx.x;
-    const float* x = sample_lo + b * ld;
-    const float* y = sample_hi + b * ld;
-    uint32_t k = static_cast<uint32_t>(sq[b].k);
-    if (threadIdx.x == 0) {
-        s_total = 0;
-        s_hits = 0;
-        s_kmin = 0xffffffffu;
-        s_kmax = 0u;
-    }
-    __syncthreads();
-    // count, and the smallest and largest key: the bits they share are
-    // shared by every key, so the digit passes start below them
-    uint32_t local = 0, kmin = 0xffffffffu, kmax = 0u;
-    for_values(x, y, n, midpoint, [&](float v) {
-        if (v == -INFINITY) return;
-        const uint32_t key = mono32(v);
-        ++local;
-        kmin = key < kmin ? key : kmin;
-        kmax = key > kmax ? key : kmax;
-    });
-    for (int off = 32; off > 0; off >>= 1) {
-        local += __shfl_xor(local, off, 64);
-        const uint32_t a = __shfl_xor(kmin, off, 64), c = __shfl_xor(kmax, off, 64);
-        kmin = a < kmin ? a : kmin;
-        kmax = c > kmax ? c : kmax;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&s_total, local);
-        atomicMin(&s_kmin, kmin);
-        atomicMax(&s_kmax, kmax);
-    }
-    __syncthreads();
-    const uint32_t total = s_total;
-    if (k == 0 || k > total) {
-        if (threadIdx.x == 0) s_tau = -INFINITY;
-    } else {
-        const uint32_t lo = s_kmin, hi = s_kmax;
-        const int common = (lo == hi) ? 32 : __clz(lo ^ hi);
-        uint32_t pmask = (common == 32) ? 0xffffffffu : ~(0xffffffffu >> common);
-        uint32_t prefix = lo & pmask;
-        // the k-th largest key, digit by digit (8 bits, the last one fewer)
-        for (int bits = 32 - common; bits > 0;) {
-            const int w = bits < 8 ? bits : 8;
-            const int shift = bits - w;
-            const uint32_t dmask = (1u << w) - 1u;
-            for (int i = threadIdx.x; i < kCopies * kStride; i += blockDim.x) hist[i] = 0;
-            __syncthreads();
-            uint32_t* mine = hist + (threadIdx.x & (kCopies - 1)) * kStride;
-            for_values(x, y, n, midpoint, [&](float v) {
-                if (v == -INFINITY) return;
-                const uint32_t key = mono32(v);
-                if ((key & pmask) == prefix) atomicAdd(&mine[(key >> shift) & dmask], 1u);
-            });
-            __syncthreads();
-            for (int d = threadIdx.x; d <= static_cast<int>(dmask); d += blockDim.x) {
-                uint32_t c = 0;
-                for (int r = 0; r < kCopies; ++r) c += hist[r * kStride + d];
-                hist[d] = c;   // copy 0 holds the sums (each d read and written by one thread)
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                uint32_t cum = 0;
-                int dgt = static_cast<int>(dmask);
-                for (; dgt > 0; --dgt) {
-                    if (cum + hist[dgt] >= k) break;
-                    cum += hist[dgt];
+                for (int e = 0; e < 4; ++e) {
+                    if ((w4[e] & 0xffffu) == 0xfc00u) continue;   // not eligible
+                    ++elig;
+#pragma unroll
+                    for (int z = 0; z < 2; ++z) {
+                        const int c = half_order(z ? w4[e] >> 16 : w4[e] & 0xffffu) - base;
+                        // at or above the first window's top: rounding only
+                        if (c >= 0 && (c < kBins || win == 0)) atomicAdd(&bins[z][c < kBins ? c : kBins - 1], 1u);
+                    }
                 }
-                s_digit = static_cast<uint32_t>(dgt);
-                s_rest = k - cum;
             }
-            __syncthreads();
-            prefix |= s_digit << shift;
-            pmask |= dmask << shift;
-            k = s_rest;
-            bits -= w;
-            __syncthreads();
         }
-        if (threadIdx.x == 0) s_tau = unmono32(prefix);
-    }
-    __syncthreads();
-    const float tau = s_tau;
-    uint32_t hits = 0;
-    for_values(y, y, n, 0, [&](float v) { hits += (v != -INFINITY && v >= tau); });
-    atomicAdd(&s_hits, hits);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        sq[b].tau = tau;
-        sq[b].sample_hits = static_cast<int32_t>(s_hits);
+        if (win == 0) {
+            for (int off = 32; off > 0; off >>= 1) elig += __shfl_xor(elig, off, 64);
+            if (lane == 0 && elig) atomicAdd(&s_elig, elig);
+        }
+        __syncthreads();
+        if (win == 0) total = s_elig;
+        if (k == 0 || k > total) {   // everything eligible is a candidate
+            if (tid == 0) {
+                sq[b].tau = -INFINITY;
+                sq[b].sample_hits = static_cast<int32_t>(total);
+            }
+            return;
+        }
+        // suffix sums of both histograms, eight bins per thread
+        uint32_t own[2], suf[2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            own[z] = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) own[z] += bins[z][8 * tid + i];
+            uint32_t v = own[z];
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t y = __shfl_down(v, off, 64);
+                if (lane + off < 64) v += y;
+            }
+            suf[z] = v;   // this lane's and the higher lanes' bins
+            if (lane == 0) s_part[z][wave] = v;
+        }
+        if (tid == 0) s_found = 0;
+        __syncthreads();
+        uint32_t all[2] = {0u, 0u};
+        for (int w = 0; w < 16; ++w)
+            for (int z = 0; z < 2; ++z) {
+                const uint32_t p = s_part[z][w];
+                all[z] += p;
+                if (w > wave) suf[z] += p;
+            }
+        uint32_t below = above[0] + suf[0] - own[0];   // values above this thread's bins
+        if (below < k && below + own[0] >= k) {        // one thread, if the window holds the k-th
+            int i = 7;
+            for (; i > 0; --i) {
+                below += bins[0][8 * tid + i];
+                if (below >= k) break;
+            }
+            s_bin = static_cast<uint32_t>(8 * tid + i);
+            s_found = 1;
+        }
+        __syncthreads();
+        if (s_found) {
+            const int bin = static_cast<int>(s_bin);
+            if (bin >= 8 * tid && bin < 8 * tid + 8) {
+                uint32_t hits = above[1] + suf[1] - own[1];
+                for (int i = 7; i >= bin - 8 * tid; --i) hits += bins[1][8 * tid + i];
+                // the largest value at most the bin's: its half float, or for a
+                // negative one (rounded up) the half float below
+                const int c = base + bin;
+                const int h = c >= 0x8000 ? c : c - 1;
+                const uint32_t bits = static_cast<uint32_t>(h >= 0x8000 ? h & 0x7fff : ~h & 0xffff);
+                _Float16 f;
+                const uint16_t b16 = static_cast<uint16_t>(bits);
+                __builtin_memcpy(&f, &b16, 2);
+                sq[b].tau = static_cast<float>(f) * pow2f(sample_exp(Q, norm_sum) - 14);
+                sq[b].sample_hits = static_cast<int32_t>(hits);
+            }
+            return;
+        }
+        above[0] += all[0];
+        above[1] += all[1];
+        if (base <= 0) {   // cannot happen (k <= total): every half float has been counted
+            if (tid == 0) {
+                sq[b].tau = -INFINITY;
+                sq[b].sample_hits = static_cast<int32_t>(total);
+            }
+            return;
+        }
+        __syncthreads();
     }
 }
 
-void launch_select(const float* sample_lo, const float* sample_hi, int64_t n, int64_t ld,
-                   bool midpoint, ScanQ* sq, int32_t nq, hipStream_t stream) {
+void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum, ScanQ* sq, int32_t nq,
+                   hipStream_t stream) {
     if (nq <= 0) return;
-    hipLaunchKernelGGL(k_select, dim3(nq), dim3(1024), 0, stream, sample_lo, sample_hi, n, ld,
-                       midpoint ? 1 : 0, sq);
+    hipLaunchKernelGGL(k_select, dim3(nq), dim3(1024), 0, stream, sample, n, ld, norm_sum, sq);
 }
 
 }  // namespace pvs

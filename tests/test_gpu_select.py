@@ -1,0 +1,63 @@
+"""Threshold selection from the sample (half-float histogram windows): the
+prefix stays exact and the scans stay selective where the k-th value lies in
+the first window, far below it (one row of a huge norm), below zero (every
+score negative), at zero, and where every value is the same; for the
+one-query, small-batch, one-, four- and eight-tile sample passes and for
+samples of every block (small n) and of some (large n)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(E, x, q, m, max_candidates=None):
+    idx = E.pvs_build(x)
+    st = E.pvs_open(idx, q)
+    ids, sc, cnt, _ = E.pvs_next(st, m)
+    assert np.all(cnt == min(m, len(x)))
+    rows = np.arange(len(x))
+    for b in range(0, len(q), max(1, len(q) // 5)):
+        s = E.pvs_scores(st, b, rows)
+        want = np.lexsort((rows, -s.astype(np.float64)))[:m]
+        assert np.array_equal(ids[b], want)
+        assert np.array_equal(sc[b] + 0.0, s[want] + 0.0)
+    st_ = E.pvs_stats(st)
+    if max_candidates is not None:
+        assert st_["candidates"] <= max_candidates * len(q), st_
+
+
+@pytest.mark.parametrize("n,d,B", [(5000, 48, 1), (5000, 48, 20), (300_001, 16, 1), (300_001, 16, 7),
+                                   (290_000, 64, 40), (270_000, 384, 40), (270_000, 384, 200), (262_144, 64, 140)])
+@pytest.mark.parametrize("kind", ["plain", "outlier", "negative", "zero", "same"])
+def test_selected_threshold(n, d, B, kind):
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(n + d + B)
+    x = rng.standard_normal((n, d), dtype=np.float32)
+    x /= np.linalg.norm(x, axis=1, keepdims=True)
+    q = rng.standard_normal((B, d), dtype=np.float32)
+    q /= np.linalg.norm(q, axis=1, keepdims=True)
+    m, limit = 300, None
+    if kind == "outlier":
+        x[n // 2] *= 1e4       # the k-th score is below 1e-4 of the index's largest bound
+    elif kind == "negative":
+        x = np.abs(x)
+        q = -np.abs(q)
+    elif kind == "zero":
+        x[:, 0] = 0
+        x[: n - 50, :] = 0     # nearly every score is exactly 0
+    elif kind == "same":
+        x[:] = x[0]
+        m = 40
+    if kind in ("plain", "outlier") and n > 200_000 and d == 64:
+        limit = n // 2
+    _check(E, x, q, m, limit)
+
+
+def test_selection_scale_extremes():
+    """Rows and queries near the ends of the float range."""
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(5)
+    for rs, qs in ((1e-18, 1e-18), (1e18, 1e15), (1e-30, 1.0), (1e15, 1e-30)):
+        x = (rng.standard_normal((6000, 32)) * rs).astype(np.float32)
+        q = (rng.standard_normal((3, 32)) * qs).astype(np.float32)
+        _check(E, x, q, 200)
