@@ -187,12 +187,13 @@ static int index_quantize(pvs_index* ix, const float* src, int64_t n, int32_t pt
         EAHR_TRY(global_scale_of(ix, src, n, dev, &ix->global_s));
     const float fixed_s = (ix->quant == EAHR_QUANT_GLOBAL) ? ix->global_s : 0.0f;
     HIP_TRY(hipMemsetAsync(ix->flags, 0, 4 * sizeof(uint32_t), s));
-    const int64_t chunk = 65536;
+    const int64_t staged = 65536;                    // rows of the staging buffer
+    const int64_t chunk = dev ? n : staged;
     for (int64_t r = 0; r < n; r += chunk) {
         const int64_t k = std::min(chunk, n - r);
         const float* p = src + r * ix->d;
         if (!dev) {
-            if (!ix->staging) EAHR_TRY(dev_alloc(&ix->staging, static_cast<size_t>(chunk) * ix->d));
+            if (!ix->staging) EAHR_TRY(dev_alloc(&ix->staging, static_cast<size_t>(staged) * ix->d));
             HIP_TRY(hipMemcpyAsync(ix->staging, p, static_cast<size_t>(k) * ix->d * sizeof(float),
                                    hipMemcpyHostToDevice, s));
             p = ix->staging;
