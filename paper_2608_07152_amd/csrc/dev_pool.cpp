@@ -1,0 +1,155 @@
+#include "dev_pool.h"
+
+#include <algorithm>
+#include <list>
+#include <mutex>
+#include <new>
+#include <unordered_map>
+#include <vector>
+
+namespace eahr {
+namespace {
+
+constexpr int kHostSlot = -1;   // "device" of pinned host memory
+
+struct Block {
+    void* p;
+    size_t bytes;
+    int where;      // device, or kHostSlot
+    int ages = 0;   // index releases it has been kept through
+};
+
+struct Pool {
+    std::mutex mu;
+    std::unordered_map<void*, Block> live;   // handed out
+    std::list<Block> kept;                   // oldest first
+};
+
+// Never destroyed: handles may be closed while the process ends, after the
+// destructors of static objects.
+Pool& pool() {
+    static Pool* p = new Pool();
+    return *p;
+}
+
+void free_block(const Block& b) {
+    if (b.where == kHostSlot) (void)hipHostFree(b.p);
+    else (void)hipFree(b.p);
+}
+
+size_t keep_limit(int where) { return where == kHostSlot ? kKeepHost : kKeepDevice; }
+
+size_t kept_bytes(const Pool& P, int where) {
+    size_t n = 0;
+    for (const auto& b : P.kept)
+        if (b.where == where) n += b.bytes;
+    return n;
+}
+
+hipError_t raw_alloc(void** p, size_t bytes, bool host) {
+    return host ? hipHostMalloc(p, bytes) : hipMalloc(p, bytes);
+}
+
+}  // namespace
+
+hipError_t pool_alloc(void** p, size_t bytes, bool host) {
+    *p = nullptr;
+    // whole pages of 4 KiB, or of 2 MiB for large blocks, so that blocks fit
+    // requests of about their size again
+    const size_t unit = bytes >= (size_t(2) << 20) ? size_t(2) << 20 : size_t(4) << 10;
+    bytes = std::max<size_t>(1, (bytes + unit - 1) / unit) * unit;
+    int where = kHostSlot;
+    if (!host) {
+        const hipError_t e = hipGetDevice(&where);
+        if (e != hipSuccess) return e;
+    }
+    Pool& P = pool();
+    try {
+        {
+            std::lock_guard<std::mutex> lk(P.mu);
+            // the smallest kept block that fits and is not much larger
+            auto best = P.kept.end();
+            for (auto it = P.kept.begin(); it != P.kept.end(); ++it)
+                if (it->where == where && it->bytes >= bytes && it->bytes <= bytes + bytes / 4 &&
+                    (best == P.kept.end() || it->bytes < best->bytes))
+                    best = it;
+            if (best != P.kept.end()) {
+                Block b = *best;
+                b.ages = 0;
+                P.live.emplace(b.p, b);
+                P.kept.erase(best);
+                *p = b.p;
+                return hipSuccess;
+            }
+        }
+        void* q = nullptr;
+        hipError_t e = raw_alloc(&q, bytes, host);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            std::list<Block> drop;
+            {
+                std::lock_guard<std::mutex> lk(P.mu);
+                for (auto it = P.kept.begin(); it != P.kept.end();) {
+                    const auto at = it++;
+                    if (at->where == where) drop.splice(drop.end(), P.kept, at);
+                }
+            }
+            for (const auto& b : drop) free_block(b);
+            e = raw_alloc(&q, bytes, host);
+        }
+        if (e != hipSuccess) return e;
+        try {
+            std::lock_guard<std::mutex> lk(P.mu);
+            P.live.emplace(q, Block{q, bytes, where});
+        } catch (...) {
+            free_block(Block{q, bytes, where});
+            return hipErrorOutOfMemory;
+        }
+        *p = q;
+        return hipSuccess;
+    } catch (const std::bad_alloc&) {
+        return hipErrorOutOfMemory;
+    }
+}
+
+void pool_release(void* p) {
+    if (!p) return;
+    Pool& P = pool();
+    std::list<Block> drop;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        const auto it = P.live.find(p);
+        if (it == P.live.end()) return;
+        const Block b = it->second;
+        P.live.erase(it);
+        try {
+            P.kept.push_back(b);
+        } catch (...) {
+            free_block(b);
+            return;
+        }
+        size_t n = kept_bytes(P, b.where);
+        for (auto k = P.kept.begin(); k != P.kept.end() && n > keep_limit(b.where);) {
+            const auto at = k++;
+            if (at->where != b.where) continue;
+            n -= at->bytes;
+            drop.splice(drop.end(), P.kept, at);
+        }
+    }
+    for (const auto& b : drop) free_block(b);
+}
+
+void pool_age() {
+    Pool& P = pool();
+    std::list<Block> drop;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        for (auto it = P.kept.begin(); it != P.kept.end();) {
+            const auto at = it++;
+            if (++at->ages > 2) drop.splice(drop.end(), P.kept, at);
+        }
+    }
+    for (const auto& b : drop) free_block(b);
+}
+
+}  // namespace eahr

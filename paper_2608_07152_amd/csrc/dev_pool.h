@@ -1,0 +1,35 @@
+// Device and pinned host memory of the library's handles.
+//
+// Allocating and freeing the storage of a segment costs more than building
+// it: 200K x 768 rows are quantised in 0.28 ms, while hipMalloc and hipFree
+// of their 0.77 GB take 1.1 ms, and 20 ms once a program frees memory faster
+// than the driver clears it.  Blocks of closed handles are therefore kept for
+// the next ones:
+//  * at most kKeepDevice bytes per GPU and kKeepHost bytes of pinned memory;
+//    past that the blocks kept longest are freed first;
+//  * a kept block that two index releases in a row find unused is freed, so a
+//    program that has moved on to other sizes gets its memory back;
+//  * when an allocation fails, every kept block of that kind is freed and the
+//    allocation tried again.
+// Any thread may call; the lock is held across the bookkeeping only.  A block
+// must be idle when it is released (no stream uses it any more), so it may be
+// handed out to any stream at once.  Its contents are not cleared.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+
+namespace eahr {
+
+constexpr size_t kKeepDevice = size_t(4) << 30;
+constexpr size_t kKeepHost = size_t(256) << 20;
+
+// At least `bytes` of memory of the current device, or of pinned host memory.
+hipError_t pool_alloc(void** p, size_t bytes, bool host);
+// Back to the pool (null is allowed).  The block must be idle.
+void pool_release(void* p);
+// An index has been released: kept blocks that were already unused at the
+// previous release are freed.
+void pool_age();
+
+}  // namespace eahr

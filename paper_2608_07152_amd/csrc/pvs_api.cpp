@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "common.h"
+#include "dev_pool.h"
 #include "eahr.h"
 #include "host_parallel.h"
 #include "pvs_internal.h"
@@ -58,14 +59,22 @@ template <typename T>
 int dev_alloc(T** p, size_t count) {
     *p = nullptr;
     if (count == 0) count = 1;
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T)));
+    HIP_TRY(::eahr::pool_alloc(reinterpret_cast<void**>(p), count * sizeof(T), false));
     return EAHR_OK;
 }
 
+// Device or pinned host memory; nothing on the GPU may still use it.
 template <typename T>
-void dev_free(T*& p) {
-    if (p) (void)hipFree(p);
+void mem_free(T*& p) {
+    ::eahr::pool_release(p);
     p = nullptr;
+}
+
+template <typename T>
+int host_alloc(T** p, size_t count) {
+    *p = nullptr;
+    HIP_TRY(::eahr::pool_alloc(reinterpret_cast<void**>(p), count * sizeof(T), true));
+    return EAHR_OK;
 }
 
 std::atomic<int> g_prof_on{0};
@@ -87,16 +96,23 @@ static void free_buffers(ScanBuffers& b);
 
 // ======================================================================= index
 pvs_index::~pvs_index() {
-    dev_free(codes);
-    dev_free(scale);
-    dev_free(vnorm);
-    dev_free(enorm);
-    dev_free(frows);
-    dev_free(live);
-    dev_free(flags);
-    dev_free(staging);
-    for (auto& s : snaps) dev_free(s.vis);
+    // the memory goes back to a pool that may hand it to any stream
+    int cur = 0;
+    const bool other = hipGetDevice(&cur) == hipSuccess && cur != device;
+    if (other) (void)hipSetDevice(device);
+    (void)hipDeviceSynchronize();
+    if (other) (void)hipSetDevice(cur);
+    mem_free(codes);
+    mem_free(scale);
+    mem_free(vnorm);
+    mem_free(enorm);
+    mem_free(frows);
+    mem_free(live);
+    mem_free(flags);
+    mem_free(staging);
+    for (auto& s : snaps) mem_free(s.vis);
     free_buffers(spare);
+    ::eahr::pool_age();
 }
 
 static int index_grow(pvs_index* ix, int64_t need_rows) {
@@ -129,12 +145,12 @@ static int index_grow(pvs_index* ix, int64_t need_rows) {
         HIP_TRY(hipMemcpyAsync(live, ix->live, ix->cap / 64 * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
     }
-    dev_free(ix->codes);
-    dev_free(ix->scale);
-    dev_free(ix->vnorm);
-    dev_free(ix->enorm);
-    dev_free(ix->frows);
-    dev_free(ix->live);
+    mem_free(ix->codes);
+    mem_free(ix->scale);
+    mem_free(ix->vnorm);
+    mem_free(ix->enorm);
+    mem_free(ix->frows);
+    mem_free(ix->live);
     ix->codes = codes;
     ix->scale = scale;
     ix->vnorm = vnorm;
@@ -229,7 +245,7 @@ static int take_snapshot(pvs_index* ix, int64_t* epoch) {
     unsigned long long h = 0;
     HIP_TRY(hipMemcpyAsync(&h, cnt, sizeof(h), hipMemcpyDeviceToHost, ix->stream));
     HIP_TRY(hipStreamSynchronize(ix->stream));
-    dev_free(cnt);
+    mem_free(cnt);
     sn.visible = static_cast<int64_t>(h);
     ix->snaps.push_back(sn);
     if (epoch) *epoch = static_cast<int64_t>(ix->snaps.size()) - 1;
@@ -300,7 +316,7 @@ extern "C" int pvs_delete(pvs_index* ix, const int64_t* ids, int64_t n) {
     pvs::launch_clear_ids(ix->live, d_ids, n, ix->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(ix->stream));
-    dev_free(d_ids);
+    mem_free(d_ids);
     return EAHR_OK;
 }
 
@@ -364,32 +380,30 @@ extern "C" int pvs_read_index(const pvs_index* ix, int64_t row0, int64_t n, int8
 
 // ======================================================================= state
 pvs_state::~pvs_state() {
-    dev_free(qcodes);
-    dev_free(qrows);
-    dev_free(qscale);
-    dev_free(qnorm);
-    dev_free(qenorm);
-    dev_free(qhnorm);
-    dev_free(qflags);
+    if (ix) (void)hipStreamSynchronize(ix->stream);   // the memory goes back to a pool
+    mem_free(qcodes);
+    mem_free(qrows);
+    mem_free(qscale);
+    mem_free(qnorm);
+    mem_free(qenorm);
+    mem_free(qhnorm);
+    mem_free(qflags);
     release_scan_buffers();
     for (auto& e : ev)
         if (e) (void)hipEventDestroy(e);
 }
 
 void pvs_state::release_scan_buffers() {
-    dev_free(scanq);
-    dev_free(counts);
-    dev_free(sample);
-    dev_free(qfrag);
-    dev_free(pairs);
-    dev_free(keys);
-    dev_free(keys_tmp);
-    if (h_scanq) (void)hipHostFree(h_scanq);
-    if (h_counts) (void)hipHostFree(h_counts);
-    if (h_packed) (void)hipHostFree(h_packed);
-    h_scanq = nullptr;
-    h_counts = nullptr;
-    h_packed = nullptr;
+    mem_free(scanq);
+    mem_free(counts);
+    mem_free(sample);
+    mem_free(qfrag);
+    mem_free(pairs);
+    mem_free(keys);
+    mem_free(keys_tmp);
+    mem_free(h_scanq);
+    mem_free(h_counts);
+    mem_free(h_packed);
     buf_nq = 0;
     buf_sample = 0;
     pool_cap = 0;
@@ -445,16 +459,16 @@ static void donate_buffers(pvs_state* st, ScanBuffers& b) {
 }
 
 static void free_buffers(ScanBuffers& b) {
-    dev_free(b.scanq);
-    dev_free(b.counts);
-    dev_free(b.sample);
-    dev_free(b.qfrag);
-    dev_free(b.pairs);
-    dev_free(b.keys);
-    dev_free(b.keys_tmp);
-    if (b.h_scanq) (void)hipHostFree(b.h_scanq);
-    if (b.h_counts) (void)hipHostFree(b.h_counts);
-    if (b.h_packed) (void)hipHostFree(b.h_packed);
+    mem_free(b.scanq);
+    mem_free(b.counts);
+    mem_free(b.sample);
+    mem_free(b.qfrag);
+    mem_free(b.pairs);
+    mem_free(b.keys);
+    mem_free(b.keys_tmp);
+    mem_free(b.h_scanq);
+    mem_free(b.h_counts);
+    mem_free(b.h_packed);
     b = ScanBuffers{};
 }
 
@@ -481,22 +495,20 @@ static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
     nq = std::max(nq, st->buf_nq);
     sample_ld = std::max(sample_ld, st->buf_sample);
     HIP_TRY(hipStreamSynchronize(st->ix->stream));
-    dev_free(st->scanq);
-    dev_free(st->counts);
-    dev_free(st->sample);
-    dev_free(st->qfrag);
-    if (st->h_scanq) (void)hipHostFree(st->h_scanq);
-    if (st->h_counts) (void)hipHostFree(st->h_counts);
-    st->h_scanq = nullptr;
-    st->h_counts = nullptr;
+    mem_free(st->scanq);
+    mem_free(st->counts);
+    mem_free(st->sample);
+    mem_free(st->qfrag);
+    mem_free(st->h_scanq);
+    mem_free(st->h_counts);
     EAHR_TRY(dev_alloc(&st->scanq, nq));
     EAHR_TRY(dev_alloc(&st->counts, all_counts(nq)));
     EAHR_TRY(dev_alloc(&st->sample, static_cast<size_t>(nq) * sample_ld));
     int8_t* f;
     EAHR_TRY(dev_alloc(&f, static_cast<size_t>(st->ix->dp / 32) * 8 * 64 * 16));
     st->qfrag = f;
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st->h_scanq), nq * sizeof(ScanQ)));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st->h_counts), all_counts(nq) * sizeof(int32_t)));
+    EAHR_TRY(host_alloc(&st->h_scanq, nq));
+    EAHR_TRY(host_alloc(&st->h_counts, all_counts(nq)));
     st->buf_nq = nq;
     st->buf_sample = sample_ld;
     return EAHR_OK;
@@ -507,9 +519,9 @@ static int ensure_pool(pvs_state* st, int64_t slots) {
     if (slots <= st->pool_cap) return EAHR_OK;
     slots = std::max<int64_t>(slots + slots / 4, pvs::kMinCap);
     HIP_TRY(hipStreamSynchronize(st->ix->stream));
-    dev_free(st->pairs);
-    dev_free(st->keys);
-    dev_free(st->keys_tmp);
+    mem_free(st->pairs);
+    mem_free(st->keys);
+    mem_free(st->keys_tmp);
     st->pool_cap = 0;
     const size_t n = static_cast<size_t>(slots);
     EAHR_TRY(dev_alloc(&st->pairs, n));
@@ -522,10 +534,9 @@ static int ensure_pool(pvs_state* st, int64_t slots) {
 static int ensure_host_packed(pvs_state* st, int64_t n) {
     if (n <= st->h_packed_cap) return EAHR_OK;
     n = std::max<int64_t>(n + n / 4, 4096);
-    if (st->h_packed) (void)hipHostFree(st->h_packed);
-    st->h_packed = nullptr;
+    mem_free(st->h_packed);
     st->h_packed_cap = 0;
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&st->h_packed), n * sizeof(uint64_t)));
+    EAHR_TRY(host_alloc(&st->h_packed, n));
     st->h_packed_cap = n;
     return EAHR_OK;
 }
@@ -597,7 +608,7 @@ extern "C" int pvs_open_gen(const pvs_index* ix, int64_t epoch, const float* q, 
     HIP_TRY(hipMemcpyAsync(nh.data(), st->qhnorm, B * sizeof(float), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(fl, st->qflags, sizeof(fl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    dev_free(tmp);
+    mem_free(tmp);
     if (fl[0]) EAHR_FAIL(EAHR_E_NONFINITE, "pvs_open: non-finite value in a query");
     st->q.resize(B);
     for (size_t b = 0; b < st->recycled.size() && b < static_cast<size_t>(B); ++b)
@@ -720,10 +731,10 @@ extern "C" int pvs_intervals(const pvs_state* st, int32_t b, const int64_t* rows
     HIP_TRY(hipMemcpyAsync(lo, dlo, n * sizeof(float), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(hi, dhi, n * sizeof(float), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    dev_free(dq);
-    dev_free(dr);
-    dev_free(dlo);
-    dev_free(dhi);
+    mem_free(dq);
+    mem_free(dr);
+    mem_free(dlo);
+    mem_free(dhi);
     return EAHR_OK;
 }
 
@@ -745,8 +756,8 @@ extern "C" int pvs_scores(const pvs_state* st, int32_t b, const int64_t* rows, i
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(scores, dout, n * sizeof(float), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    dev_free(dr);
-    dev_free(dout);
+    mem_free(dr);
+    mem_free(dout);
     return EAHR_OK;
 }
 
@@ -861,11 +872,11 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
             return EAHR_OK;
         };
         rc = body();
-        dev_free(keys);
-        dev_free(tmp);
-        dev_free(d_qidx);
-        dev_free(d_cnt);
-        dev_free(d_sq);
+        mem_free(keys);
+        mem_free(tmp);
+        mem_free(d_qidx);
+        mem_free(d_cnt);
+        mem_free(d_sq);
         if (rc != EAHR_OK) return rc;
         if (prof) {
             float t0 = 0.0f, t1 = 0.0f;

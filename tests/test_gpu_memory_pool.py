@@ -1,0 +1,88 @@
+"""Memory of closed handles is reused, bounded and given back; results do not
+depend on whose memory a handle reuses, from one thread or several."""
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _first_ids(E, x, q, m):
+    idx = E.pvs_build(x)
+    st = E.pvs_open(idx, q)
+    ids, sc, _, _ = E.pvs_next(st, m)
+    E.pvs_close(st)
+    E.pvs_free(idx)
+    return ids, sc
+
+
+def _want(x, q, m):
+    return np.argsort(-(q.astype(np.float64) @ x.astype(np.float64).T), axis=1, kind="stable")[:, :m]
+
+
+def test_segments_built_and_freed_in_turn():
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(0)
+    for i in range(12):
+        n, d = int(rng.integers(100, 30_000)), int(rng.integers(8, 300))
+        x = rng.standard_normal((n, d)).astype(np.float32)
+        q = rng.standard_normal((int(rng.integers(1, 40)), d)).astype(np.float32)
+        ids, _ = _first_ids(E, x, q, 10)
+        assert np.array_equal(ids, _want(x, q, 10)), (i, n, d)
+
+
+def test_threads_with_streams_of_their_own():
+    import torch
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(1)
+    xs = [rng.standard_normal((20_000, 64)).astype(np.float32) for _ in range(4)]
+    qs = [rng.standard_normal((5, 64)).astype(np.float32) for _ in range(4)]
+    bad = []
+
+    def work(t):
+        try:
+            s = torch.cuda.Stream()
+            for _ in range(10):
+                idx = E.pvs_build(xs[t], stream=s)
+                st = E.pvs_open(idx, qs[t])
+                ids = E.pvs_next(st, 20)[0]
+                E.pvs_close(st)
+                E.pvs_free(idx)
+                if not np.array_equal(ids, _want(xs[t], qs[t], 20)):
+                    bad.append(t)
+        except Exception as e:   # noqa: BLE001
+            bad.append((t, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
+
+
+def test_memory_is_given_back():
+    import torch
+    from paper_2608_07152_amd import eahr as E
+    q = np.ones((1, 256), np.float32)
+    small = np.ones((64, 256), np.float32)
+    _first_ids(E, small, q, 5)
+    for _ in range(4):      # whatever earlier work left
+        E.pvs_free(E.pvs_build(small))
+    before = torch.cuda.mem_get_info()[0]
+    big = torch.ones(1_000_000, 256, device="cuda")
+    idx = E.pvs_build(big)                      # 1.3 GB, kept when freed
+    del big
+    torch.cuda.empty_cache()
+    E.pvs_free(idx)
+    assert before - torch.cuda.mem_get_info()[0] <= (4 << 30) + (64 << 20)
+    huge = torch.ones(5_000_000, 256, device="cuda")
+    idx = E.pvs_build(huge)                     # 6.4 GB: more than is ever kept
+    del huge
+    torch.cuda.empty_cache()
+    E.pvs_free(idx)
+    assert before - torch.cuda.mem_get_info()[0] <= (4 << 30) + (64 << 20)
+    for _ in range(4):
+        E.pvs_free(E.pvs_build(small))
+    assert before - torch.cuda.mem_get_info()[0] <= 64 << 20
