@@ -473,12 +473,12 @@ static void free_buffers(ScanBuffers& b) {
 }
 
 // Per-query scan buffers for nq queries and samples of sample_ld rows.
-// counts layout: [cert nq][fail nq][unused nq + 2][rescore chunk base kSub + 1], then from pair_counts_at(nq) the kSub append
+// counts layout: [cert nq * kCertStride][fail nq][rescore chunk base kSub + 1], then from pair_counts_at(nq) the kSub append
 // counters of the pair pool, from reads_counts_at(nq) the kSub row-load
 // counters of rescoring, kCntStride ints apart, and from evals_counts_at(nq)
 // the records of each query.  h_counts mirrors it.
 static size_t pair_counts_at(int32_t nq) {
-    return (3 * static_cast<size_t>(nq) + 2 + pvs::kSub + 1 + 63) / 64 * 64;
+    return ((pvs::kCertStride + 1) * static_cast<size_t>(nq) + pvs::kSub + 1 + 63) / 64 * 64;
 }
 static size_t reads_counts_at(int32_t nq) {
     return pair_counts_at(nq) + static_cast<size_t>(pvs::kSub) * pvs::kCntStride;
@@ -858,7 +858,7 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
             pvs::launch_full_keys(v, st->vis, n, st->qrows, d_qidx, ng, keys, n, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[1], s));
-            const uint64_t* sorted = pvs::launch_segmented_sort(keys, tmp, d_cnt, d_sq, ng, n, nullptr, s);
+            const uint64_t* sorted = pvs::launch_segmented_sort(keys, tmp, d_cnt, 1, d_sq, ng, n, nullptr, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[2], s));
             for (int32_t i = 0; i < ng; ++i) {
@@ -1023,9 +1023,9 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     EAHR_TRY(ensure_pool(st, total));
     HIP_TRY(hipMemcpyAsync(st->scanq, st->h_scanq, nq * sizeof(ScanQ), hipMemcpyHostToDevice, s));
     int32_t* d_cert = st->counts;
-    int32_t* d_fail = st->counts + nq;
+    int32_t* d_fail = st->counts + static_cast<size_t>(nq) * pvs::kCertStride;
     int32_t* d_reads = st->counts + reads_counts_at(nq);
-    int32_t* d_cbase = st->counts + 3 * nq + 2;
+    int32_t* d_cbase = d_fail + nq;
     int32_t* d_pcnt = st->counts + pair_counts_at(nq);
     const int32_t* h_pcnt = st->h_counts + pair_counts_at(nq);
     const int64_t pair_sub = total / pvs::kSub;
@@ -1096,27 +1096,30 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     EAHR_TRY(mark(4));
     // only the certified keys are ordered; a query whose key region overflowed
     // (it is scanned again) keeps the region's worth
-    HIP_TRY(hipMemcpyAsync(st->h_counts, d_cert, 2 * static_cast<size_t>(nq) * sizeof(int32_t),
+    HIP_TRY(hipMemcpyAsync(st->h_counts, d_cert, (pvs::kCertStride + 1) * static_cast<size_t>(nq) * sizeof(int32_t),
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     tp[3] = clk::now();
-    const std::vector<int32_t> cert_all(st->h_counts, st->h_counts + nq);
+    std::vector<int32_t> cert_all(nq), h_cert(nq);
     int64_t max_cert = 0;
     bool clamped = false;
     for (int32_t i = 0; i < nq; ++i) {
+        int32_t& c = st->h_counts[static_cast<size_t>(i) * pvs::kCertStride];
+        cert_all[i] = c;
         const int64_t region = pvs::kSub * st->h_scanq[i].cand_cap;
-        if (st->h_counts[i] > region) {
-            st->h_counts[i] = static_cast<int32_t>(region);
+        if (c > region) {
+            c = static_cast<int32_t>(region);
             clamped = true;
         }
-        max_cert = std::max<int64_t>(max_cert, st->h_counts[i]);
+        h_cert[i] = c;
+        max_cert = std::max<int64_t>(max_cert, c);
     }
     if (clamped)
-        HIP_TRY(hipMemcpyAsync(d_cert, st->h_counts, nq * sizeof(int32_t), hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync(d_cert, st->h_counts, pvs::kCertStride * static_cast<size_t>(nq) * sizeof(int32_t),
+                               hipMemcpyHostToDevice, s));
     // the packed layout: query i's keys at h_offs[i] (the sort takes the same
     // prefix of the same counts)
-    const int32_t* h_cert = st->h_counts;
-    const int32_t* h_fail = st->h_counts + nq;
+    const int32_t* h_fail = st->h_counts + static_cast<size_t>(nq) * pvs::kCertStride;
     std::vector<int64_t> h_offs(static_cast<size_t>(nq) + 1, 0);
     for (int32_t i = 0; i < nq; ++i) h_offs[i + 1] = h_offs[i] + h_cert[i];
     const int64_t n_packed = h_offs[nq];
@@ -1127,7 +1130,7 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     // and costs a launch).  They stay there (pending) until the next scan
     // round, which appends them to the caches, while the ranks they hold are
     // emitted straight from the copy.
-    pvs::launch_segmented_sort(st->keys, st->keys_tmp, d_cert, st->scanq, nq, max_cert, st->h_packed, s);
+    pvs::launch_segmented_sort(st->keys, st->keys_tmp, d_cert, pvs::kCertStride, st->scanq, nq, max_cert, st->h_packed, s);
     EAHR_TRY(mark(5));
     HIP_TRY(hipGetLastError());
     if (prof)

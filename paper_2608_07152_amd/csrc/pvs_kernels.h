@@ -17,6 +17,11 @@ constexpr int kMaxMfmaQueries = 256;  // queries per MFMA scan pass (8 tiles of 
 // of one.  Counters sit kCntStride ints (64 bytes) apart.
 constexpr int kSub = 64;
 constexpr int kCntStride = 16;
+// The counters of certified keys, one per query of a scan, sit kCertStride
+// ints (a cache line) apart: concurrent additions to one line are applied one
+// after another (next to each other, 256 counters held the rescoring of 9.8M
+// pairs at d = 384 to 2.59 ms; apart it takes 1.20 ms).
+constexpr int kCertStride = 32;
 
 // Per scanning query, uploaded before every scan.  All fields are read
 // uniformly by a wavefront (scalar loads).
@@ -112,7 +117,7 @@ void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum
 // pair_sub each, in chunks of kRescoreChunk; chunks = rescore_chunks of the
 // host copy of the counters), computes each pair's float32 score and checks
 // it against its interval, and appends the keys of the certified pairs of
-// query b at keys[cand_off + j], j < min(cert_cnt[b], kSub * cand_cap)
+// query b at keys[cand_off + j], j < min(cert_cnt[b * kCertStride], kSub * cand_cap)
 // (cert_cnt zeroed by the caller counts them all; order of appends
 // unspecified).  cbase is device scratch of kSub + 1 ints; the kSub counters
 // row_reads[s * kCntStride] (zeroed by the caller) sum to the number of row
@@ -135,12 +140,12 @@ void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, in
 void launch_full_keys(const IndexView& ix, const uint64_t* vis, int64_t n_rows, const float* qrows,
                       const int32_t* qidx, int32_t ng, uint64_t* keys, int64_t ld,
                       hipStream_t stream);
-// Sorts every query's candidate keys (cnt[b] keys from cand_off) ascending;
+// Sorts every query's candidate keys (cnt[b * cnt_ld] keys from cand_off) ascending;
 // returns the buffer holding the result: keys or tmp (each query's keys from
 // its cand_off), or, when given, packed, with the queries' keys one after
 // another.  packed may be pinned host memory: only the last kernel writes it,
 // and nothing reads it.
-uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt,
+uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt, int32_t cnt_ld,
                                 const ScanQ* sq, int32_t nq, int64_t max_cnt, uint64_t* packed,
                                 hipStream_t stream);
 

@@ -152,7 +152,7 @@ __device__ __forceinline__ void rescore_quarter(
         todo &= ~grp;
     }
     int base = 0;
-    if (cert && lane == leader) base = atomicAdd(&cert_cnt[myb], size);
+    if (cert && lane == leader) base = atomicAdd(&cert_cnt[myb * kCertStride], size);
     base = __shfl(base, leader, 64);
     if (!cert) return;
     const int64_t pos = static_cast<int64_t>(base) + rank;
@@ -276,11 +276,11 @@ void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, in
 
 // Where query b's keys start when the queries' keys lie one after another:
 // the sum of the counts before it, taken by the whole workgroup.
-__device__ __forceinline__ int64_t packed_offset(const int32_t* __restrict__ cnt, int b) {
+__device__ __forceinline__ int64_t packed_offset(const int32_t* __restrict__ cnt, int cnt_ld, int b) {
     __shared__ int64_t part[16];
     const int waves = static_cast<int>(blockDim.x >> 6), wave = static_cast<int>(threadIdx.x >> 6);
     int64_t x = 0;
-    for (int i = threadIdx.x; i < b; i += blockDim.x) x += cnt[i];
+    for (int i = threadIdx.x; i < b; i += blockDim.x) x += cnt[i * cnt_ld];
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     if ((threadIdx.x & 63) == 0) part[wave] = x;
     __syncthreads();
@@ -357,19 +357,19 @@ __device__ __forceinline__ uint64_t lane_xor(uint64_t x) {
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void k_sort_tiles(const uint64_t* __restrict__ keys,
                                                            uint64_t* __restrict__ dst, int packed,
-                                                           const int32_t* __restrict__ cnt,
+                                                           const int32_t* __restrict__ cnt, int cnt_ld,
                                                            const ScanQ* __restrict__ sq) {
     constexpr int PER = 8;
     constexpr int T = 64 * WAVES * PER;
     __shared__ uint64_t s[T];
     const int tid = threadIdx.x;
     const int b = blockIdx.y;
-    const int64_t n = cnt[b];
+    const int64_t n = cnt[b * cnt_ld];
     const int64_t base = static_cast<int64_t>(blockIdx.x) * T;
     if (base >= n) return;
     const int m = static_cast<int>(min(static_cast<int64_t>(T), n - base));
     const uint64_t* k = keys + sq[b].cand_off + base;
-    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off) + base;
+    uint64_t* d = dst + (packed ? packed_offset(cnt, cnt_ld, b) : sq[b].cand_off) + base;
     uint64_t v[PER];
     // any assignment of the unsorted keys to threads will do: the coalesced one
 #pragma unroll
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_sort_tiles(const uint64_t* __res
 // eight consecutive outputs after a search of its own diagonal there.
 __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
                                                uint64_t* __restrict__ dst, int packed,
-                                               const int32_t* __restrict__ cnt,
+                                               const int32_t* __restrict__ cnt, int cnt_ld,
                                                const ScanQ* __restrict__ sq, int64_t run) {
     constexpr int T = kSortTile;
     constexpr int PER = T / 256;
@@ -457,12 +457,12 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
     __shared__ uint64_t out[T];
     __shared__ int64_t s_split[2];
     const int b = blockIdx.y;
-    const int64_t n = cnt[b];
+    const int64_t n = cnt[b * cnt_ld];
     const int64_t o0 = static_cast<int64_t>(blockIdx.x) * T;
     if (o0 >= n) return;
     const int64_t o1 = min(o0 + T, n);
     const uint64_t* s = src + sq[b].cand_off;
-    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off);
+    uint64_t* d = dst + (packed ? packed_offset(cnt, cnt_ld, b) : sq[b].cand_off);
     const int64_t start = (o0 / (2 * run)) * (2 * run);
     const int64_t mid = min(start + run, n);
     const int64_t end = min(start + 2 * run, n);
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
 // (one tile of 512 takes 7.3 us, of 2,048 11.3 us; a merge level of a few
 // thousand keys takes 8 us and its launch).  Longer lists start from 4,096:
 // a tile of 8,192 keys took 37 us, more than two of its halves and a merge.
-uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt,
+uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt, int32_t cnt_ld,
                                 const ScanQ* sq, int32_t nq, int64_t max_cnt, uint64_t* packed,
                                 hipStream_t stream) {
     if (nq <= 0 || max_cnt <= 0) return packed ? packed : keys;
@@ -531,18 +531,18 @@ uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cn
     uint64_t* a = (packed && tile >= max_cnt) ? packed : keys;
     const int direct = a == packed;
     if (tile == 512)
-        hipLaunchKernelGGL(k_sort_tiles<1>, grid, dim3(64), 0, stream, keys, a, direct, cnt, sq);
+        hipLaunchKernelGGL(k_sort_tiles<1>, grid, dim3(64), 0, stream, keys, a, direct, cnt, cnt_ld, sq);
     else if (tile == 2048)
-        hipLaunchKernelGGL(k_sort_tiles<4>, grid, dim3(256), 0, stream, keys, a, direct, cnt, sq);
+        hipLaunchKernelGGL(k_sort_tiles<4>, grid, dim3(256), 0, stream, keys, a, direct, cnt, cnt_ld, sq);
     else
-        hipLaunchKernelGGL(k_sort_tiles<8>, grid, dim3(512), 0, stream, keys, a, direct, cnt, sq);
+        hipLaunchKernelGGL(k_sort_tiles<8>, grid, dim3(512), 0, stream, keys, a, direct, cnt, cnt_ld, sq);
     uint64_t* b = tmp;
     for (int64_t run = tile; run < max_cnt; run *= 2) {
         const int64_t g = (max_cnt + kSortTile - 1) / kSortTile;
         const bool last = 2 * run >= max_cnt;
         if (last && packed) b = packed;
         hipLaunchKernelGGL(k_merge, dim3(static_cast<uint32_t>(g), nq), dim3(256), 0, stream, a, b,
-                           last && packed ? 1 : 0, cnt, sq, run);
+                           last && packed ? 1 : 0, cnt, cnt_ld, sq, run);
         uint64_t* t = a;
         a = b;
         b = t;
