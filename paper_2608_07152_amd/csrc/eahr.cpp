@@ -211,8 +211,10 @@ static int topk_impl(const pvs_index* dense, int64_t epoch, pvs_merge* merged,
         }
     } cl;
     const auto t_open = std::chrono::steady_clock::now();
-    if (use_dense && !merged)
+    if (use_dense && !merged) {
         EAHR_TRY(pvs_open_gen(dense, epoch, q_dense, B, q_ptr_kind, ep.dense_generator, &cl.st));
+        pvs_expect_depth(cl.st);
+    }
     const double open_dense_ms = ms_since(t_open);
     // sparse states are opened by the sparse workers, at a query's first
     // call; the queries are checked here

@@ -576,6 +576,7 @@ extern "C" int pvs_open_gen(const pvs_index* ix, int64_t epoch, const float* q, 
     st->n_rows = ix->snaps[epoch].rows;
     st->n_vis = ix->snaps[epoch].visible;
     st->vis = ix->snaps[epoch].vis;
+    st->reads_on = ix->read_on.load(std::memory_order_relaxed) > 0;
     if (ix->has_spare) {
         adopt_buffers(st.get(), ix->spare);
         ix->has_spare = false;
@@ -640,6 +641,10 @@ extern "C" void pvs_close(pvs_state* st) {
     const pvs_index* ix = st->ix;
     if (ix) {
         (void)hipStreamSynchronize(ix->stream);
+        if (!st->expected && st->calls > 0) {
+            const int had = ix->read_on.load(std::memory_order_relaxed);
+            ix->read_on.store(st->calls > 1 ? 2 : std::max(0, had - 1), std::memory_order_relaxed);
+        }
         if (!ix->has_spare) {
             donate_buffers(st, ix->spare);
             ix->has_spare = true;
@@ -935,7 +940,10 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     const double frac = static_cast<double>(nsb) / static_cast<double>(nblocks);
     EAHR_TRY(ensure_query_buffers(st, nq, sample_ld));
 
-    const int64_t mmin = std::max<int64_t>(pvs::kTargetMin, std::min<int64_t>(pvs::kTargetMax, pvs::kTargetBudget / nq));
+    const int64_t ahead = std::min(pvs::kSpecFloorBudget, st->n_rows / 16);   // ranks ahead that a scan pays for
+    const int64_t floor_all = std::min(pvs::kSpecFloorBudget, st->n_rows / 4);
+    const int64_t mmin = std::max<int64_t>(
+        pvs::kTargetMin, std::min({pvs::kTargetMax, pvs::kTargetBudget / nq, ahead / nq}));
     for (int32_t i = 0; i < nq; ++i) {
         const int32_t b = todo[i];
         auto& Q = st->q[b];
@@ -943,13 +951,17 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         const int64_t have = static_cast<int64_t>(Q.cache.size());
         const int64_t avail = have - Q.emitted;
         const int64_t need = std::max<int64_t>(1, m - avail);
-        const int64_t spec_floor = std::max(pvs::kSpecFloor, pvs::kSpecFloorBudget / nq);
-        const int64_t spec = st->spec_off ? 0
-                           : std::min(std::max(pvs::kSpecFactor * (Q.emitted + m), spec_floor) - have,
-                                      pvs::kSpecBudget / nq);
-        const int64_t target = std::max({need, mmin, spec}) + lower_overlap(st, b);
+        const int64_t factor = !st->reads_on && Q.scans == 1 ? pvs::kSpecSecond : pvs::kSpecFactor;
+        const int64_t depth = !st->reads_on && Q.scans == 0
+                            ? ahead / nq
+                            : std::max({factor * (Q.emitted + m), pvs::kSpecFloor, floor_all / nq}) - have;
+        const int64_t spec = st->spec_off ? 0 : std::min(depth, pvs::kSpecBudget / nq);
+        const int64_t overlap = lower_overlap(st, b);
+        const int64_t target = std::max({need, mmin, spec}) + overlap;
+        const double nf = static_cast<double>(need + overlap) * frac;
         double k = (stride == 1) ? static_cast<double>(target)
-                                 : std::max(4.0, std::ceil(pvs::kSampleMargin * target * frac));
+                                 : std::ceil(std::max(pvs::kSampleMargin * target * frac,
+                                                      nf + pvs::kSampleSigmas * std::sqrt(nf) + 4.0));
         for (int r = 0; r < Q.retries; ++r) k *= 4.0;
         sq.k = static_cast<int32_t>(std::min(k, 2.0e9));
         st->h_scanq[i] = sq;
@@ -1209,6 +1221,7 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         }
         Q.cap_hint = 0;
         const int64_t c = h_cert[i];
+        Q.scans += c > 0;
         st->stats.certified += c;
         if (c > 0) {
             const uint64_t last = st->h_packed[h_offs[i] + c - 1];
@@ -1238,6 +1251,7 @@ static int next_ranks(pvs_state* st, int32_t m, const uint8_t* active, int64_t* 
                       int32_t* count, int32_t* status) {
     const int32_t B = st->B;
     std::vector<int32_t> todo;
+    st->calls += m > 0;
     for (int32_t b = 0; b < B; ++b) {
         if (active && !active[b]) continue;
         auto& Q = st->q[b];
@@ -1357,6 +1371,10 @@ void pvs_retire(pvs_state* st, int32_t b) {
     auto& Q = st->q[b];
     Q.retired = true;
     Q.pend_n = 0;
+}
+
+void pvs_expect_depth(pvs_state* st) {
+    if (st) st->reads_on = st->expected = true;
 }
 
 bool pvs_query_failed(const pvs_state* st, int32_t b) {

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <mutex>
 #include <vector>
@@ -22,7 +23,10 @@ namespace pvs {
 // interval midpoints (close to the scores, so the rows certified, s >= tau,
 // number about the target scaled by the stride) with this relative margin.
 constexpr int64_t kSampleBlocks = 2048;
+// The request itself is certified with five standard deviations of its count
+// in the sample, because falling short costs another scan.
 constexpr double kSampleMargin = 1.25;
+constexpr double kSampleSigmas = 5.0;
 // Smallest candidate pool allocated for a scan, and the largest pool one scan
 // round may use (queries beyond it wait for the next round).
 constexpr int64_t kMinCap = 4096;
@@ -46,7 +50,7 @@ constexpr int64_t kTargetBudget = 8192;
 // to an extra scan.  Measured on 8.8M x 768 (queries/s at batch 256 / 1 / 64):
 // factor 8 and 2^20 ranks 1,860 / 90 / 1,085; 8 and 2^22 2,355 / 106 / 1,128;
 // 16 and 2^22 2,338 / 117 / 1,241; 2^23 and 2^24 are slower again.
-// A scan certifies at least max(kSpecFloor, kSpecFloorBudget / queries)
+// A scan certifies at least max(kSpecFloor, min(kSpecFloorBudget, rows / 4) / queries)
 // ranks per query (within the same budget): a round of a batch scan costs
 // about as much as rescoring a few thousand ranks per query, and a round of
 // a single-query scan (the whole code array streamed once) as much as
@@ -55,6 +59,19 @@ constexpr int64_t kTargetBudget = 8192;
 // 2^18 247 (4096 alone: 182; batches of 64 and 256 unchanged).  Re-measured
 // after the other changes (ms per batch-256 / batch-64 step): floor 4096 and
 // 2^22 ranks 94.8 / 43.3; 8192 99.9 / 49.0; 2048 100.5 / 46.1; 2^23 94.4 / 44.0.
+//
+// A caller that asks once pays for ranks nobody reads, one that reads on for
+// another scan.  So the first scan of a state certifies the request and about
+// min(2^17, rows / 16) ranks ahead over its queries (rescoring them costs at
+// most about an eighth of streaming the codes), unless its caller always
+// reads on (eahr_topk, merges: pvs_expect_depth) or the last states closed on
+// the index did; the second scan takes kSpecSecond in place of the factor.
+// Certified 16 requests ahead at once, 256 queries for 1,000 ranks on
+// 1M x 384 took 3,010 us and 256 for 100 on 8.8M x 768 4,950; as now 980 and
+// 2,910.  Never predicting that a caller reads on made 4 of 12 paging
+// programs slower than before (7 doubling pages of 640 for 64 queries on
+// 4M x 768: 15.8 instead of 12.4 ms).
+constexpr int64_t kSpecSecond = 4;
 constexpr int64_t kSpecFactor = 16;
 constexpr int64_t kSpecBudget = int64_t(1) << 22;
 constexpr int64_t kSpecFloor = 4096;
@@ -85,6 +102,9 @@ int pvs_fill_exact(pvs_state* st, int64_t depth, const uint8_t* active, int64_t*
 // query's certified keys that are still in a scan's pinned copy are not
 // moved to its cache any more, and pvs_next / pvs_fill skip the query.
 void pvs_retire(pvs_state* st, int32_t b);
+// The caller will read on, deeper with each call: the state's first scan
+// certifies as far ahead as later ones.
+void pvs_expect_depth(pvs_state* st);
 // Whether query b of a state has failed (a rescored score outside its
 // interval), also in work-ahead that pvs_next has not reported yet.
 bool pvs_query_failed(const pvs_state* st, int32_t b);
@@ -146,6 +166,9 @@ struct pvs_index {
     std::vector<Snapshot> snaps;
     mutable ScanBuffers spare;   // buffers of the last closed state
     mutable bool has_spare = false;
+    // whether the states closed last read on past their first request: 2
+    // after one that did, one less after each that did not
+    mutable std::atomic<int> read_on{0};
     // states opened on the index and not closed yet; pvs_free while some are
     // open only marks the index, and the last pvs_close releases it
     mutable std::mutex life_mu;
@@ -171,6 +194,7 @@ struct pvs_state {
         bool failed = false;
         bool cert_exhausted = false;    // every visible row certified
         int retries = 0;                // consecutive scans that certified too few
+        int scans = 0;                  // scans that certified ranks for it
         int64_t cap_hint = 0;           // candidate capacity needed by the last overflow
         int64_t evals = 0;              // (query, row) pairs rescored in float32
     };
@@ -201,6 +225,9 @@ struct pvs_state {
     uint64_t* keys_tmp = nullptr;
     pvs::ScanPath path = pvs::ScanPath::Auto;
     bool spec_off = false;             // scans certify no further ahead than asked
+    bool reads_on = false;             // the first scan certifies as far ahead as later ones
+    bool expected = false;             // its caller said so (pvs_expect_depth)
+    int64_t calls = 0;                 // pvs_next calls that asked for ranks
     // test knob: first-attempt key regions and pool divided by this, so that
     // the overflow and rescan paths run (results do not change)
     int64_t cap_shrink = 1;

@@ -346,9 +346,11 @@ extern "C" int pvs_merge_open(const pvs_index* const* segs, const int64_t* epoch
         if (versions && versions[s]) S.version.assign(versions[s], versions[s] + erows);
     }
     init_sources(mg.get());
-    for (int32_t s = 0; s < n_segs; ++s)
+    for (int32_t s = 0; s < n_segs; ++s) {
         EAHR_TRY(pvs_open_gen(segs[s], epochs ? epochs[s] : 0, q, B, ptr_kind, EAHR_GEN_INTERVALS,
                               &mg->src[s].st));
+        pvs_expect_depth(mg->src[s].st);
+    }
     // the visible rows of every Segment's snapshot
     for (int32_t s = 0; s < n_segs; ++s) {
         const auto& S = mg->src[s];
