@@ -47,7 +47,8 @@ size_t kept_bytes(const Pool& P, int where) {
 }
 
 hipError_t raw_alloc(void** p, size_t bytes, bool host) {
-    return host ? hipHostMalloc(p, bytes) : hipMalloc(p, bytes);
+    // pinned memory that kernels of every GPU may write
+    return host ? hipHostMalloc(p, bytes, hipHostMallocPortable | hipHostMallocMapped) : hipMalloc(p, bytes);
 }
 
 }  // namespace

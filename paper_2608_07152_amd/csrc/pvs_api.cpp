@@ -383,11 +383,6 @@ pvs_state::~pvs_state() {
     if (ix) (void)hipStreamSynchronize(ix->stream);   // the memory goes back to a pool
     mem_free(qcodes);
     mem_free(qrows);
-    mem_free(qscale);
-    mem_free(qnorm);
-    mem_free(qenorm);
-    mem_free(qhnorm);
-    mem_free(qflags);
     release_scan_buffers();
     for (auto& e : ev)
         if (e) (void)hipEventDestroy(e);
@@ -473,10 +468,13 @@ static void free_buffers(ScanBuffers& b) {
 }
 
 // Per-query scan buffers for nq queries and samples of sample_ld rows.
-// counts layout: [cert nq * kCertStride][fail nq][rescore chunk base kSub + 1], then from pair_counts_at(nq) the kSub append
-// counters of the pair pool, from reads_counts_at(nq) the kSub row-load
-// counters of rescoring, kCntStride ints apart, and from evals_counts_at(nq)
-// the records of each query.  h_counts mirrors it.
+// counts layout: [cert nq * kCertStride][fail nq][rescore chunk base kSub + 1],
+// then from pair_counts_at(nq) the kSub append counters of the pair pool, from
+// reads_counts_at(nq) the kSub row-load counters of rescoring, kCntStride ints
+// apart, and from evals_counts_at(nq) the records of each query in kSub
+// copies.  h_counts (pinned) holds what kernels report: [sampled hits nq]
+// [records nq][certified nq][failed nq][append counters kSub], then the
+// row-load counters as on the device (profiling only).
 static size_t pair_counts_at(int32_t nq) {
     return ((pvs::kCertStride + 1) * static_cast<size_t>(nq) + pvs::kSub + 1 + 63) / 64 * 64;
 }
@@ -488,6 +486,9 @@ static size_t evals_counts_at(int32_t nq) {
 }
 static size_t all_counts(int32_t nq) {
     return evals_counts_at(nq) + static_cast<size_t>(pvs::kSub) * nq;
+}
+static size_t report_counts(int32_t nq) {
+    return 4 * static_cast<size_t>(nq) + pvs::kSub + static_cast<size_t>(pvs::kSub) * pvs::kCntStride;
 }
 
 static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
@@ -508,7 +509,7 @@ static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
     EAHR_TRY(dev_alloc(&f, static_cast<size_t>(st->ix->dp / 32) * 8 * 64 * 16));
     st->qfrag = f;
     EAHR_TRY(host_alloc(&st->h_scanq, nq));
-    EAHR_TRY(host_alloc(&st->h_counts, all_counts(nq)));
+    EAHR_TRY(host_alloc(&st->h_counts, report_counts(nq)));
     st->buf_nq = nq;
     st->buf_sample = sample_ld;
     return EAHR_OK;
@@ -584,12 +585,11 @@ extern "C" int pvs_open_gen(const pvs_index* ix, int64_t epoch, const float* q, 
     hipStream_t s = ix->stream;
     EAHR_TRY(dev_alloc(&st->qcodes, static_cast<size_t>(B) * ix->dp));
     EAHR_TRY(dev_alloc(&st->qrows, static_cast<size_t>(B) * ix->df));
-    EAHR_TRY(dev_alloc(&st->qscale, B));
-    EAHR_TRY(dev_alloc(&st->qnorm, B));
-    EAHR_TRY(dev_alloc(&st->qenorm, B));
-    EAHR_TRY(dev_alloc(&st->qhnorm, B));
-    EAHR_TRY(dev_alloc(&st->qflags, 4));
-    HIP_TRY(hipMemsetAsync(st->qflags, 0, 4 * sizeof(uint32_t), s));
+    struct HostMeta {   // pinned, written by the kernel
+        pvs::QueryMeta* p = nullptr;
+        ~HostMeta() { mem_free(p); }
+    } hm;
+    EAHR_TRY(host_alloc(&hm.p, B));
     const float* src = q;
     float* tmp = nullptr;
     if (ptr_kind == EAHR_PTR_HOST) {
@@ -598,19 +598,14 @@ extern "C" int pvs_open_gen(const pvs_index* ix, int64_t epoch, const float* q, 
                                hipMemcpyHostToDevice, s));
         src = tmp;
     }
-    pvs::launch_quantize(src, B, ix->d, ix->d, 0, false, st->qcodes, ix->dp, st->qscale, st->qnorm,
-                         st->qenorm, st->qhnorm, st->qrows, ix->df, 0.0f, st->qflags, s);
-    HIP_TRY(hipGetLastError());
-    std::vector<float> sc(B), nq(B), ne(B), nh(B);
-    uint32_t fl[4];
-    HIP_TRY(hipMemcpyAsync(sc.data(), st->qscale, B * sizeof(float), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(nq.data(), st->qnorm, B * sizeof(float), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(ne.data(), st->qenorm, B * sizeof(float), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(nh.data(), st->qhnorm, B * sizeof(float), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(fl, st->qflags, sizeof(fl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    pvs::launch_quantize(src, B, ix->d, ix->d, 0, false, st->qcodes, ix->dp, nullptr, nullptr, nullptr,
+                         hm.p, st->qrows, ix->df, 0.0f, nullptr, s);
+    const hipError_t le = hipGetLastError(), se = hipStreamSynchronize(s);
     mem_free(tmp);
-    if (fl[0]) EAHR_FAIL(EAHR_E_NONFINITE, "pvs_open: non-finite value in a query");
+    HIP_TRY(le);
+    HIP_TRY(se);
+    for (int32_t b = 0; b < B; ++b)
+        if (hm.p[b].bad) EAHR_FAIL(EAHR_E_NONFINITE, "pvs_open: non-finite value in a query");
     st->q.resize(B);
     for (size_t b = 0; b < st->recycled.size() && b < static_cast<size_t>(B); ++b)
         st->q[b].cache.swap(st->recycled[b]);
@@ -618,14 +613,15 @@ extern "C" int pvs_open_gen(const pvs_index* ix, int64_t epoch, const float* q, 
     const double NV = ix->nv_max, NEV = ix->nev_max, g = ix->gamma;
     for (int32_t b = 0; b < B; ++b) {
         auto& Q = st->q[b];
-        Q.sq = sc[b];
-        Q.nq = nq[b];
-        Q.neq = ne[b];
-        Q.nqh = nh[b];
+        const pvs::QueryMeta& M = hm.p[b];
+        Q.sq = M.s;
+        Q.nq = M.norm;
+        Q.neq = M.enorm;
+        Q.nqh = M.hnorm;
         // bound of E + G over every row: |c| <= ||q_hat|| (||v|| + ||e_v||)
-        const double E = ne[b] * NV + nh[b] * NEV;
-        const double c = nh[b] * (NV + NEV);
-        const double G = (c + E + nq[b] * NV) * g;
+        const double E = M.enorm * NV + M.hnorm * NEV;
+        const double c = M.hnorm * (NV + NEV);
+        const double G = (c + E + M.norm * NV) * g;
         Q.wmax = static_cast<float>((E + G) * 1.01 + 1e-30);
     }
     {
@@ -976,8 +972,11 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         return EAHR_OK;
     };
     const pvs::IndexView v = view_of(ix);
+    const int32_t nq0 = nq;
     auto scan = [&](bool sample, const pvs::ScanOut& o, int32_t n) {
-        if (mfma) pvs::launch_scan_mfma(v, st->vis, nblocks, st->qcodes, st->scanq, n, ix->gamma, sample, o, st->qfrag, s);
+        // the main pass of the sampled queries finds their fragments in place
+        const bool frag = !sample && n == nq0 && n <= pvs::kMaxMfmaQueries;
+        if (mfma) pvs::launch_scan_mfma(v, st->vis, nblocks, st->qcodes, st->scanq, n, ix->gamma, sample, o, st->qfrag, frag, s);
         else pvs::launch_scan(v, st->vis, nblocks, st->qcodes, st->scanq, n, ix->gamma, sample, o, s);
     };
 
@@ -986,7 +985,13 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     clk::time_point tp[5];
     tp[0] = clk::now();
     // 1. threshold and candidate estimate from the sampled blocks
-    HIP_TRY(hipMemcpyAsync(st->scanq, st->h_scanq, nq * sizeof(ScanQ), hipMemcpyHostToDevice, s));
+    int32_t* const h_hits = st->h_counts;
+    int32_t* const h_evals = h_hits + nq;
+    int32_t* const h_call = h_evals + nq;      // certified keys, also past the key regions
+    int32_t* const h_fail = h_call + nq;
+    int32_t* const h_pcnt = h_fail + nq;
+    int32_t* const h_reads = h_pcnt + pvs::kSub;
+    pvs::launch_round_begin(st->h_scanq, st->scanq, nq, st->counts, static_cast<int64_t>(all_counts(nq)), s);
     pvs::ScanOut so;
     so.sample = st->sample;
     so.sample_mid = stride > 1 ? 1 : 0;
@@ -995,10 +1000,9 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     so.sample_stride = stride;
     EAHR_TRY(mark(0));
     scan(true, so, nq);
-    pvs::launch_select(st->sample, sample_ld, sample_ld, so.norm_sum, st->scanq, nq, s);
+    pvs::launch_select(st->sample, sample_ld, sample_ld, so.norm_sum, st->scanq, nq, h_hits, s);
     EAHR_TRY(mark(1));
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(st->h_scanq, st->scanq, nq * sizeof(ScanQ), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     tp[1] = clk::now();
 
@@ -1010,11 +1014,11 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     for (; run < nq; ++run) {
         ScanQ& sq = st->h_scanq[run];
         const auto& Q = st->q[todo[run]];
-        // exact count when the sample saw every block, plus room for the
-        // unused tails of per-workgroup slices (at most cap / 16)
+        // exact count when the sample saw every block, plus some room
+        const int64_t hits = h_hits[run];
         const int64_t cap = (stride == 1)
-                          ? static_cast<int64_t>(sq.sample_hits) + sq.sample_hits / 8 + 64
-                          : static_cast<int64_t>(std::ceil(sq.sample_hits / frac * pvs::kCapSlack)) + pvs::kCapPad;
+                          ? hits + hits / 8 + 64
+                          : static_cast<int64_t>(std::ceil(hits / frac * pvs::kCapSlack)) + pvs::kCapPad;
         // per sub-region, with room for an uneven split
         int64_t sub = (cap + pvs::kSub - 1) / pvs::kSub;
         sub += sub / 4 + 16;
@@ -1033,16 +1037,14 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     todo.resize(run);
     nq = run;
     EAHR_TRY(ensure_pool(st, total));
-    HIP_TRY(hipMemcpyAsync(st->scanq, st->h_scanq, nq * sizeof(ScanQ), hipMemcpyHostToDevice, s));
+    pvs::launch_regions(st->h_scanq, st->scanq, nq, s);
     int32_t* d_cert = st->counts;
     int32_t* d_fail = st->counts + static_cast<size_t>(nq) * pvs::kCertStride;
     int32_t* d_reads = st->counts + reads_counts_at(nq);
     int32_t* d_cbase = d_fail + nq;
     int32_t* d_pcnt = st->counts + pair_counts_at(nq);
-    const int32_t* h_pcnt = st->h_counts + pair_counts_at(nq);
     const int64_t pair_sub = total / pvs::kSub;
-    HIP_TRY(hipMemsetAsync(st->counts, 0, all_counts(nq) * sizeof(int32_t), s));
-    pvs::ScanOut mo;
+    pvs::ScanOut mo;   // its counters, cleared for nq0 >= nq queries
     mo.pairs = st->pairs;
     mo.pair_sub = pair_sub;
     mo.pair_cnt = d_pcnt;
@@ -1051,29 +1053,44 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     EAHR_TRY(mark(2));
     scan(false, mo, nq);
     EAHR_TRY(mark(3));
+    pvs::launch_scan_report(d_pcnt, pair_sub, d_cbase, mo.q_evals, nq, h_pcnt, h_evals, s);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(st->h_counts + pair_counts_at(nq), d_pcnt,
-                           static_cast<size_t>(pvs::kSub) * pvs::kCntStride * sizeof(int32_t),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(st->h_counts + evals_counts_at(nq), mo.q_evals,
-                           static_cast<size_t>(pvs::kSub) * nq * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    tp[2] = clk::now();
+    const bool one_wait = total <= pvs::kOneWaitSlots;
     int64_t kept = 0, fullest = 0;   // records kept; the fullest sub-region's count
-    for (int i = 0; i < pvs::kSub; ++i) {
-        const int64_t c = h_pcnt[i * pvs::kCntStride];
-        kept += std::min(c, pair_sub);
-        fullest = std::max(fullest, c);
+    auto read_counters = [&]() {
+        for (int i = 0; i < pvs::kSub; ++i) {
+            kept += std::min<int64_t>(h_pcnt[i], pair_sub);
+            fullest = std::max<int64_t>(fullest, h_pcnt[i]);
+        }
+    };
+    int64_t chunks = pvs::kSub * ((pair_sub + pvs::kRescoreChunk - 1) / pvs::kRescoreChunk);
+    if (!one_wait) {
+        HIP_TRY(hipStreamSynchronize(s));
+        read_counters();
+        chunks = pvs::rescore_chunks(h_pcnt, pair_sub);
     }
-    const bool pool_over = fullest > pair_sub;   // records were dropped
+    tp[2] = clk::now();
+    // 3. rescore (not when records were dropped), order and pack the certified
+    //    ranks
+    if (fullest <= pair_sub) {
+        pvs::launch_rescore(v, st->qrows, st->scanq, nq, d_pcnt, st->pairs, pair_sub, d_cbase, chunks,
+                            ix->gamma, st->keys, d_cert, d_fail, d_reads, st->test_fail_qi, s);
+        EAHR_TRY(mark(4));
+        // only the certified keys are ordered; a query whose key region
+        // overflowed (it is scanned again) keeps the region's worth
+        pvs::launch_cert_report(d_cert, d_fail, st->scanq, nq, h_call, h_fail, s);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(s));
+        if (one_wait) read_counters();
+    }
+    tp[3] = clk::now();
     st->stats.scans += 1;
     st->stats.sample_scans += 1;
     st->stats.rows_scanned += nblocks * 64;
     st->stats.bytes_scanned += st->n_rows * (static_cast<int64_t>(ix->d) + 12) + nblocks * 8;
-    if (pool_over) {
-        // records were dropped: nothing of this scan is used, so nothing is
-        // rescored, and every query scans again with room for all of its
-        // candidates
+    if (fullest > pair_sub) {
+        // records were dropped: nothing of this scan is used, and every query
+        // scans again with room for all of its candidates
         const double grow = static_cast<double>(fullest) / static_cast<double>(pair_sub);
         std::vector<int32_t> again;
         for (int32_t i = 0; i < nq; ++i) {
@@ -1095,43 +1112,16 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         todo.swap(again);
         return EAHR_OK;
     }
-    {
-        const int32_t* ev = st->h_counts + evals_counts_at(nq);
-        for (int c = 0; c < pvs::kSub; ++c)
-            for (int32_t i = 0; i < nq; ++i) st->q[todo[i]].evals += ev[c * nq + i];
-    }
-
-    // 3. rescore, order and pack the certified ranks
-    const int64_t chunks = pvs::rescore_chunks(h_pcnt, pair_sub);
-    pvs::launch_rescore(v, st->qrows, st->scanq, nq, d_pcnt, st->pairs, pair_sub, d_cbase, chunks,
-                        ix->gamma, st->keys, d_cert, d_fail, d_reads, st->test_fail_qi, s);
-    EAHR_TRY(mark(4));
-    // only the certified keys are ordered; a query whose key region overflowed
-    // (it is scanned again) keeps the region's worth
-    HIP_TRY(hipMemcpyAsync(st->h_counts, d_cert, (pvs::kCertStride + 1) * static_cast<size_t>(nq) * sizeof(int32_t),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    tp[3] = clk::now();
-    std::vector<int32_t> cert_all(nq), h_cert(nq);
+    for (int32_t i = 0; i < nq; ++i) st->q[todo[i]].evals += h_evals[i];
+    // certified keys that fit each query's region; the packed layout: query
+    // i's keys at h_offs[i] (the sort takes the same prefix of the same counts)
+    const std::vector<int32_t> cert_all(h_call, h_call + nq);
+    std::vector<int32_t> h_cert(nq);
     int64_t max_cert = 0;
-    bool clamped = false;
     for (int32_t i = 0; i < nq; ++i) {
-        int32_t& c = st->h_counts[static_cast<size_t>(i) * pvs::kCertStride];
-        cert_all[i] = c;
-        const int64_t region = pvs::kSub * st->h_scanq[i].cand_cap;
-        if (c > region) {
-            c = static_cast<int32_t>(region);
-            clamped = true;
-        }
-        h_cert[i] = c;
-        max_cert = std::max<int64_t>(max_cert, c);
+        h_cert[i] = static_cast<int32_t>(std::min<int64_t>(cert_all[i], pvs::kSub * st->h_scanq[i].cand_cap));
+        max_cert = std::max<int64_t>(max_cert, h_cert[i]);
     }
-    if (clamped)
-        HIP_TRY(hipMemcpyAsync(d_cert, st->h_counts, pvs::kCertStride * static_cast<size_t>(nq) * sizeof(int32_t),
-                               hipMemcpyHostToDevice, s));
-    // the packed layout: query i's keys at h_offs[i] (the sort takes the same
-    // prefix of the same counts)
-    const int32_t* h_fail = st->h_counts + static_cast<size_t>(nq) * pvs::kCertStride;
     std::vector<int64_t> h_offs(static_cast<size_t>(nq) + 1, 0);
     for (int32_t i = 0; i < nq; ++i) h_offs[i + 1] = h_offs[i] + h_cert[i];
     const int64_t n_packed = h_offs[nq];
@@ -1146,14 +1136,14 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
     EAHR_TRY(mark(5));
     HIP_TRY(hipGetLastError());
     if (prof)
-        HIP_TRY(hipMemcpyAsync(st->h_counts + reads_counts_at(nq), d_reads,
+        HIP_TRY(hipMemcpyAsync(h_reads, d_reads,
                                static_cast<size_t>(pvs::kSub) * pvs::kCntStride * sizeof(int32_t),
                                hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     tp[4] = clk::now();
     int64_t row_reads = 0;
     if (prof)
-        for (int i = 0; i < pvs::kSub; ++i) row_reads += st->h_counts[reads_counts_at(nq) + i * pvs::kCntStride];
+        for (int i = 0; i < pvs::kSub; ++i) row_reads += h_reads[i * pvs::kCntStride];
     std::vector<uint8_t> usable(nq, 0);
     for (int32_t i = 0; i < nq; ++i) {
         usable[i] = !h_fail[i] && cert_all[i] == h_cert[i];

@@ -81,6 +81,10 @@ constexpr int64_t kSpecFloorBudget = int64_t(1) << 17;
 // queries in one pass.  EAHR_SCAN_PATH=gemv|mfma forces one path (testing).
 constexpr int32_t kMfmaMinQueries = 9;
 enum class ScanPath { Auto, Gemv, Mfma };
+// Candidate pools of at most this many slots are rescored without waiting for
+// the scan's counters: the grid is sized for a full pool, and its empty
+// workgroups cost less than the wait (about 15 us of an idle GPU).
+constexpr int64_t kOneWaitSlots = int64_t(1) << 20;
 }  // namespace pvs
 
 // Whether pvs_next(m) on the active queries would be served from certified
@@ -206,8 +210,6 @@ struct pvs_state {
     const uint64_t* vis = nullptr;
     int8_t* qcodes = nullptr;   // B x dp row-major
     float* qrows = nullptr;     // B x df
-    float *qscale = nullptr, *qnorm = nullptr, *qenorm = nullptr, *qhnorm = nullptr;
-    uint32_t* qflags = nullptr;
     std::vector<Query> q;
     std::vector<KeyCache> recycled;   // caches adopted from the index
     pvs_counters stats{};

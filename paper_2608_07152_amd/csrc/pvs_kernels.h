@@ -38,7 +38,7 @@ struct ScanQ {
     float nqh;         // ||q_hat||_2 rounded up
     float neq;         // ||e_q||_2 rounded up
     float wmax;        // upper bound of E + G over every row of the index
-    int32_t sample_hits;  // sampled eligible rows with hi >= tau (select pass)
+    int32_t pad;
     int64_t cand_off;  // first slot of this query's key region
     int64_t cand_cap;  // its key region holds kSub * cand_cap keys
 };
@@ -57,10 +57,19 @@ struct IndexView {
     int32_t d, dp, df, nchunk;
 };
 
-// Launchers (all asynchronous on `stream`).
+// An encoded query: s_q, ||q||, ||e_q||, ||q_hat|| (rounded up), and whether it
+// holds a non-finite value.
+struct QueryMeta {
+    float s, norm, enorm, hnorm;
+    uint32_t bad;
+};
+
+// Launchers (all asynchronous on `stream`).  Kernels that hand a few numbers
+// to the host write them into pinned host memory themselves: a copy costs a
+// launch of its own and more host time than one.
 void launch_quantize(const float* src, int64_t nrows, int32_t d, int64_t src_stride,
                      int64_t row0, bool tiled, int8_t* codes, int32_t dp, float* scale,
-                     float* vnorm, float* enorm, float* hnorm, float* rows, int32_t df,
+                     float* vnorm, float* enorm, QueryMeta* qmeta, float* rows, int32_t df,
                      float fixed_s, uint32_t* flags, hipStream_t stream);
 // Largest |x| of count floats into flags[3] (float bits), non-finite into flags[0].
 void launch_maxabs(const float* src, int64_t count, uint32_t* flags, hipStream_t stream);
@@ -101,17 +110,34 @@ void launch_scan(const IndexView& ix, const uint64_t* vis, int64_t nblocks, cons
                  hipStream_t stream);
 
 // Int8 MFMA variant (same outputs as launch_scan).  `frag` is device scratch
-// of (dp / 32) * 8 KiB for the query codes in MFMA operand order.
+// of (dp / 32) * 8 KiB for the query codes in MFMA operand order; have_frag: it
+// still holds those of the same nq <= kMaxMfmaQueries queries.
 void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const int8_t* qcodes, const ScanQ* sq, int32_t nq, float gamma, bool sample,
-                      const ScanOut& o, void* frag, hipStream_t stream);
+                      const ScanOut& o, void* frag, bool have_frag, hipStream_t stream);
 int mfma_tiles_for(int32_t nq);
 
 // tau = the k-th largest selection value of each query's sample, rounded down
-// to a half float (-inf when fewer than k pairs are eligible); sample_hits =
-// sampled pairs with hi >= tau (both written into sq).
+// to a half float (-inf when fewer than k pairs are eligible), into sq; the
+// number of sampled pairs of query b with hi >= tau to h_hits[b] (pinned).
 void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum, ScanQ* sq, int32_t nq,
-                   hipStream_t stream);
+                   int32_t* h_hits, hipStream_t stream);
+
+// Start of a scan round: sq = the host's h_sq, and ncounts (a multiple of 4)
+// counters cleared.
+void launch_round_begin(const ScanQ* h_sq, ScanQ* sq, int32_t nq, int32_t* counts, int64_t ncounts,
+                        hipStream_t stream);
+// The key regions (cand_off, cand_cap) of the host's h_sq into sq.
+void launch_regions(const ScanQ* h_sq, ScanQ* sq, int32_t nq, hipStream_t stream);
+// After a main pass: the chunk bases of rescoring (cbase, kSub + 1 ints), and
+// to the host each sub-region's counter (h_pcnt) and each query's records
+// (h_evals, the sum of the kSub copies).
+void launch_scan_report(const int32_t* pair_cnt, int64_t pair_sub, int32_t* cbase, const int32_t* q_evals,
+                        int32_t nq, int32_t* h_pcnt, int32_t* h_evals, hipStream_t stream);
+// After rescoring: to the host each query's count of certified keys and its
+// failure; the device's count is cut to the query's key region.
+void launch_cert_report(int32_t* cert_cnt, const int32_t* fail, const ScanQ* sq, int32_t nq,
+                        int32_t* h_cert, int32_t* h_fail, hipStream_t stream);
 
 // Rescoring reads the kept records of every sub-region of the pool (at most
 // pair_sub each, in chunks of kRescoreChunk; chunks = rescore_chunks of the
@@ -119,7 +145,8 @@ void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum
 // it against its interval, and appends the keys of the certified pairs of
 // query b at keys[cand_off + j], j < min(cert_cnt[b * kCertStride], kSub * cand_cap)
 // (cert_cnt zeroed by the caller counts them all; order of appends
-// unspecified).  cbase is device scratch of kSub + 1 ints; the kSub counters
+// unspecified).  cbase: the chunk bases of launch_scan_report; chunks: their
+// number, or any larger one (workgroups past it end at once); the kSub counters
 // row_reads[s * kCntStride] (zeroed by the caller) sum to the number of row
 // loads, one per run of records of one row inside a wavefront's share.
 // fail_qi (tests only, -1 otherwise): the state query whose rescored scores
@@ -130,7 +157,7 @@ constexpr int kRescoreChunk = 256;
 int64_t rescore_chunks(const int32_t* pair_cnt, int64_t pair_sub);
 void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, int32_t nq,
                     const int32_t* pair_cnt, const uint4* pairs, int64_t pair_sub,
-                    int32_t* cbase, int64_t chunks, float gamma, uint64_t* keys,
+                    const int32_t* cbase, int64_t chunks, float gamma, uint64_t* keys,
                     int32_t* cert_cnt, int32_t* fail, int32_t* row_reads, int32_t fail_qi,
                     hipStream_t stream);
 

@@ -15,7 +15,8 @@ namespace pvs {
 // registers between the maximum and the codes when NV > 0: d <= 256 NV;
 // NV = 0 reads the row again).  A workgroup takes the rows of one 16-aligned
 // group of a block and writes their codes through LDS, 256 contiguous bytes
-// per chunk; a query batch (not tiled) takes four rows, one per wavefront.
+// per chunk; a query batch (not tiled) takes four rows, one per wavefront, and
+// its scales and norms go to qmeta (pinned host memory).
 // Bound by HBM (4 d read, 5 d + 12 written a row): 0.28 ms for 200K x 768 rows (5 TB/s).
 // Two atomic maxima per row on two addresses took 4.65 ms there; now a
 // workgroup issues one for all of its rows, and only when it would raise the
@@ -26,7 +27,7 @@ template <int NV>
 __global__ __launch_bounds__(256) void k_quantize(
     const float* __restrict__ src, int64_t nrows, int32_t d, int64_t src_stride, int vec, int64_t row0,
     int tiled, int8_t* __restrict__ codes, int32_t dp, float* __restrict__ scale,
-    float* __restrict__ vnorm, float* __restrict__ enorm, float* __restrict__ hnorm,
+    float* __restrict__ vnorm, float* __restrict__ enorm, QueryMeta* __restrict__ qmeta,
     float* __restrict__ rows, int32_t df, float fixed_s, uint32_t* __restrict__ flags) {
     extern __shared__ __align__(16) unsigned char q_lds[];   // tiled: [kQuantRows][dp + 16]
     __shared__ float s_max[2][4];
@@ -69,7 +70,8 @@ __global__ __launch_bounds__(256) void k_quantize(
                 for (int c = lane; c < nw; c += 64) look(load(c));
             }
             mu = wave_max(mu);
-            any_bad |= __any(bad);
+            const bool row_bad = __any(bad);
+            any_bad |= row_bad;
             float s = mu / 127.0f;
             if (mu > 0.0f && s == 0.0f) s = __uint_as_float(1u);
             if (mu == 0.0f) s = 1.0f;
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(256) void k_quantize(
                     const double e = static_cast<double>(xs[i]) - vh;
                     n2 += static_cast<double>(xs[i]) * static_cast<double>(xs[i]);
                     e2 += e * e;
-                    if (hnorm) h2 += vh * vh;
+                    if (qmeta) h2 += vh * vh;
                     word |= static_cast<uint32_t>(static_cast<uint8_t>(z)) << (8 * i);
                 }
                 if (tiled) *reinterpret_cast<uint32_t*>(q_lds + rr * pitch + 4 * c) = word;
@@ -101,16 +103,19 @@ __global__ __launch_bounds__(256) void k_quantize(
             }
             n2 = wave_sum(n2);
             e2 = wave_sum(e2);
-            if (hnorm) h2 = wave_sum(h2);
+            if (qmeta) h2 = wave_sum(h2);
             const float vn = up32(sqrt(n2));
             const float en = up32(sqrt(e2));
             top_v = fmaxf(top_v, vn);
             top_e = fmaxf(top_e, en);
             if (lane == 0) {
-                scale[R] = s;
-                vnorm[R] = vn;
-                enorm[R] = en;
-                if (hnorm) hnorm[R] = up32(sqrt(h2));
+                if (qmeta) {
+                    qmeta[R] = QueryMeta{s, vn, en, up32(sqrt(h2)), row_bad ? 1u : 0u};
+                } else {
+                    scale[R] = s;
+                    vnorm[R] = vn;
+                    enorm[R] = en;
+                }
             }
         }
         if (tiled) {   // the group's codes, sixteen rows' bytes of a chunk together
@@ -125,6 +130,7 @@ __global__ __launch_bounds__(256) void k_quantize(
             __syncthreads();
         }
     }
+    if (qmeta) return;
     if (lane == 0) {
         s_max[0][wave] = top_v;
         s_max[1][wave] = top_e;
@@ -141,7 +147,7 @@ __global__ __launch_bounds__(256) void k_quantize(
 
 void launch_quantize(const float* src, int64_t nrows, int32_t d, int64_t src_stride, int64_t row0,
                      bool tiled, int8_t* codes, int32_t dp, float* scale, float* vnorm,
-                     float* enorm, float* hnorm, float* rows, int32_t df, float fixed_s,
+                     float* enorm, QueryMeta* qmeta, float* rows, int32_t df, float fixed_s,
                      uint32_t* flags, hipStream_t stream) {
     if (nrows <= 0) return;
     const int64_t per = tiled ? kQuantRows : 4;
@@ -151,7 +157,7 @@ void launch_quantize(const float* src, int64_t nrows, int32_t d, int64_t src_str
     const int vec = (reinterpret_cast<uintptr_t>(src) % 16 == 0 && src_stride % 4 == 0) ? 1 : 0;
 #define PVS_QZ(N)                                                                                        \
     hipLaunchKernelGGL(k_quantize<N>, grid, dim3(256), lds, stream, src, nrows, d, src_stride, vec, row0, \
-                       tiled ? 1 : 0, codes, dp, scale, vnorm, enorm, hnorm, rows, df, fixed_s, flags)
+                       tiled ? 1 : 0, codes, dp, scale, vnorm, enorm, qmeta, rows, df, fixed_s, flags)
     switch ((dp + 255) / 256) {
         case 1: PVS_QZ(1); break;
         case 2: PVS_QZ(2); break;

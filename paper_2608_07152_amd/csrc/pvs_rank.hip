@@ -16,21 +16,93 @@
 
 namespace pvs {
 
-// Records of a scan round are cut into chunks of kRescoreChunk per pool
+// ------------------------------------------------------------ bookkeeping
+// Bound by launch latency, all of them: each stands for the copies and clears
+// of its place in a round (13 of the 20 launches of a one-query call were
+// copies and clears; on 20K x 128 the call took 181 us, now 107).
+__global__ __launch_bounds__(256) void k_round_begin(const uint4* __restrict__ h_sq, uint4* __restrict__ sq,
+                                                     int32_t n_sq, uint4* __restrict__ counts, int64_t n_counts) {
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * 256;
+    for (int64_t i = i0; i < n_sq; i += step) sq[i] = h_sq[i];
+    for (int64_t i = i0; i < n_counts; i += step) counts[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+void launch_round_begin(const ScanQ* h_sq, ScanQ* sq, int32_t nq, int32_t* counts, int64_t ncounts,
+                        hipStream_t stream) {
+    const int32_t n_sq = nq * static_cast<int32_t>(sizeof(ScanQ) / sizeof(uint4));
+    const int64_t blocks = std::min<int64_t>(64, (std::max<int64_t>(n_sq, ncounts / 4) + 255) / 256);
+    hipLaunchKernelGGL(k_round_begin, dim3(static_cast<uint32_t>(std::max<int64_t>(1, blocks))), dim3(256), 0, stream,
+                       reinterpret_cast<const uint4*>(h_sq), reinterpret_cast<uint4*>(sq), n_sq,
+                       reinterpret_cast<uint4*>(counts), ncounts / 4);
+}
+
+__global__ __launch_bounds__(256) void k_regions(const ScanQ* __restrict__ h_sq, ScanQ* __restrict__ sq, int32_t nq) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= nq) return;
+    sq[i].cand_off = h_sq[i].cand_off;
+    sq[i].cand_cap = h_sq[i].cand_cap;
+}
+
+void launch_regions(const ScanQ* h_sq, ScanQ* sq, int32_t nq, hipStream_t stream) {
+    if (nq > 0) hipLaunchKernelGGL(k_regions, dim3((nq + 255) / 256), dim3(256), 0, stream, h_sq, sq, nq);
+}
+
+// The records of a scan round are cut into chunks of kRescoreChunk per pool
 // sub-region; cbase[s] is the first chunk of sub-region s (exclusive prefix).
-__global__ __launch_bounds__(64) void k_chunk_base(const int32_t* __restrict__ pair_cnt,
-                                                   int64_t pair_sub, int32_t* __restrict__ cbase) {
-    if (threadIdx.x == 0) {
-        int32_t acc = 0;
-        for (int s = 0; s < kSub; ++s) {
-            cbase[s] = acc;
-            const int64_t n = pair_cnt[s * kCntStride] < pair_sub ? pair_cnt[s * kCntStride] : pair_sub;
-            acc += static_cast<int32_t>((n + kRescoreChunk - 1) / kRescoreChunk);
+__global__ __launch_bounds__(256) void k_scan_report(const int32_t* __restrict__ pair_cnt, int64_t pair_sub,
+                                                     int32_t* __restrict__ cbase, const int32_t* __restrict__ q_evals,
+                                                     int32_t nq, int32_t* __restrict__ h_pcnt,
+                                                     int32_t* __restrict__ h_evals) {
+    static_assert(kSub == 64, "one sub-region per lane");
+    if (blockIdx.x == 0 && threadIdx.x < kSub) {
+        const int s = threadIdx.x;
+        const int32_t c = pair_cnt[s * kCntStride];
+        h_pcnt[s] = c;
+        const int64_t n = c < pair_sub ? c : pair_sub;
+        const int32_t own = static_cast<int32_t>((n + kRescoreChunk - 1) / kRescoreChunk);
+        int32_t x = own;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(x, off, 64);
+            if (s >= off) x += y;
         }
-        cbase[kSub] = acc;
+        cbase[s] = x - own;
+        if (s == kSub - 1) cbase[kSub] = x;
+    }
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < nq) {
+        int32_t e = 0;
+        for (int c = 0; c < kSub; ++c) e += q_evals[c * nq + i];
+        h_evals[i] = e;
     }
 }
 
+void launch_scan_report(const int32_t* pair_cnt, int64_t pair_sub, int32_t* cbase, const int32_t* q_evals,
+                        int32_t nq, int32_t* h_pcnt, int32_t* h_evals, hipStream_t stream) {
+    hipLaunchKernelGGL(k_scan_report, dim3(std::max(1, (nq + 255) / 256)), dim3(256), 0, stream, pair_cnt, pair_sub,
+                       cbase, q_evals, nq, h_pcnt, h_evals);
+}
+
+__global__ __launch_bounds__(256) void k_cert_report(int32_t* __restrict__ cert_cnt, const int32_t* __restrict__ fail,
+                                                     const ScanQ* __restrict__ sq, int32_t nq,
+                                                     int32_t* __restrict__ h_cert, int32_t* __restrict__ h_fail) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= nq) return;
+    const int32_t c = cert_cnt[i * kCertStride];
+    h_cert[i] = c;
+    h_fail[i] = fail[i];
+    const int64_t region = kSub * sq[i].cand_cap;
+    if (c > region) cert_cnt[i * kCertStride] = static_cast<int32_t>(region);
+}
+
+void launch_cert_report(int32_t* cert_cnt, const int32_t* fail, const ScanQ* sq, int32_t nq,
+                        int32_t* h_cert, int32_t* h_fail, hipStream_t stream) {
+    if (nq > 0)
+        hipLaunchKernelGGL(k_cert_report, dim3((nq + 255) / 256), dim3(256), 0, stream, cert_cnt, fail, sq, nq, h_cert,
+                           h_fail);
+}
+
+// --------------------------------------------------------------- rescoring
 // The records of quarter `wave` of chunk x (one wavefront, 64 records).
 // Lane j first prepares record j (its interval from the recorded dot with
 // the scan's arithmetic, its query's tau and last certified key); each
@@ -177,6 +249,7 @@ __global__ __launch_bounds__(LDSQ ? 1024 : 256) void k_rescore(
     int32_t fail_qi) {
     if constexpr (LDSQ) {
         extern __shared__ float4 s_q[];   // query row b at s_q[b * df4]
+        if (static_cast<int>(blockIdx.x) * 4 >= cbase[kSub]) return;   // the same in every thread
         for (int k = threadIdx.x; k < nq * df4; k += blockDim.x) {
             const int b = k / df4;
             s_q[k] = qrows[static_cast<int64_t>(sq[b].qi) * df4 + (k - b * df4)];
@@ -188,6 +261,7 @@ __global__ __launch_bounds__(LDSQ ? 1024 : 256) void k_rescore(
                                            pair_sub, scale, vnorm, enorm, gamma, keys, cert_cnt, fail, row_reads,
                                            fail_qi);
     } else {
+        if (static_cast<int>(blockIdx.x) >= cbase[kSub]) return;
         rescore_quarter<J, FULL, false>(blockIdx.x, threadIdx.x >> 6, rows, df4, qrows, sq, cbase, pair_cnt, pairs,
                                         pair_sub, scale, vnorm, enorm, gamma, keys, cert_cnt, fail, row_reads,
                                         fail_qi);
@@ -233,7 +307,7 @@ static void rescore_j(const IndexView& ix, const float* qrows, const ScanQ* sq, 
 int64_t rescore_chunks(const int32_t* pair_cnt, int64_t pair_sub) {
     int64_t c = 0;
     for (int s = 0; s < kSub; ++s) {
-        const int64_t n = std::min<int64_t>(pair_cnt[s * kCntStride], pair_sub);
+        const int64_t n = std::min<int64_t>(pair_cnt[s], pair_sub);
         c += (n + kRescoreChunk - 1) / kRescoreChunk;
     }
     return c;
@@ -241,10 +315,9 @@ int64_t rescore_chunks(const int32_t* pair_cnt, int64_t pair_sub) {
 
 void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, int32_t nq,
                     const int32_t* pair_cnt, const uint4* pairs, int64_t pair_sub,
-                    int32_t* cbase, int64_t chunks, float gamma, uint64_t* keys,
+                    const int32_t* cbase, int64_t chunks, float gamma, uint64_t* keys,
                     int32_t* cert_cnt, int32_t* fail, int32_t* row_reads, int32_t fail_qi,
                     hipStream_t stream) {
-    hipLaunchKernelGGL(k_chunk_base, dim3(1), dim3(64), 0, stream, pair_cnt, pair_sub, cbase);
     if (chunks <= 0) return;
     const int J = group_chunks(ix.df);
     const bool full = J > 0 && ix.df / 4 == 16 * J;

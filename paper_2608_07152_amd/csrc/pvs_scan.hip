@@ -1050,13 +1050,14 @@ int mfma_tiles_for(int32_t nq) {
 
 void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const int8_t* qcodes, const ScanQ* sq, int32_t nq, float gamma, bool sample,
-                      const ScanOut& o, void* frag, hipStream_t stream) {
+                      const ScanOut& o, void* frag, bool have_frag, hipStream_t stream) {
     for (int32_t q0 = 0; q0 < nq; q0 += kMaxMfmaQueries) {
         const int32_t n = (nq - q0 < kMaxMfmaQueries) ? (nq - q0) : kMaxMfmaQueries;
         const int nqt = mfma_tiles_for(n);
         const ScanQ* s = sq + q0;
-        hipLaunchKernelGGL(k_qfrag, dim3((ix.dp / 32) * nqt), dim3(64), 0, stream, qcodes, ix.dp, s,
-                           n, nqt, static_cast<uint4*>(frag));
+        if (!have_frag)
+            hipLaunchKernelGGL(k_qfrag, dim3((ix.dp / 32) * nqt), dim3(64), 0, stream, qcodes, ix.dp, s,
+                               n, nqt, static_cast<uint4*>(frag));
         const v4i* qf = static_cast<const v4i*>(frag);
         const ScanOut so = shift_out(o, q0);
 #define PVS_MFMA_CASE(N)                                                          \
@@ -1077,7 +1078,7 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
 
 // ------------------------------------------------------------ threshold
 // tau = the k-th largest selection value of a query's sample, to the half
-// float it is kept as, and sample_hits = sampled pairs with hi >= tau.
+// float it is kept as, and the number of sampled pairs with hi >= tau.
 //
 // One pass over the sample counts both halves of every pair in two LDS
 // histograms, one bin per half float, over a window of 8,192 of them: eight
@@ -1097,7 +1098,8 @@ __device__ __forceinline__ int half_order(uint32_t h) {
 }
 
 __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sample, int64_t n,
-                                                 int64_t ld, float norm_sum, ScanQ* __restrict__ sq) {
+                                                 int64_t ld, float norm_sum, ScanQ* __restrict__ sq,
+                                                 int32_t* __restrict__ h_hits) {
     __shared__ uint32_t bins[2][kBins];
     __shared__ uint32_t s_part[2][16];
     __shared__ uint32_t s_elig, s_bin, s_found;
@@ -1146,7 +1148,7 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
         if (k == 0 || k > total) {   // everything eligible is a candidate
             if (tid == 0) {
                 sq[b].tau = -INFINITY;
-                sq[b].sample_hits = static_cast<int32_t>(total);
+                h_hits[b] = static_cast<int32_t>(total);
             }
             return;
         }
@@ -1199,7 +1201,7 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
                 const uint16_t b16 = static_cast<uint16_t>(bits);
                 __builtin_memcpy(&f, &b16, 2);
                 sq[b].tau = static_cast<float>(f) * pow2f(sample_exp(Q, norm_sum) - 14);
-                sq[b].sample_hits = static_cast<int32_t>(hits);
+                h_hits[b] = static_cast<int32_t>(hits);
             }
             return;
         }
@@ -1208,7 +1210,7 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
         if (base <= 0) {   // cannot happen (k <= total): every half float has been counted
             if (tid == 0) {
                 sq[b].tau = -INFINITY;
-                sq[b].sample_hits = static_cast<int32_t>(total);
+                h_hits[b] = static_cast<int32_t>(total);
             }
             return;
         }
@@ -1217,9 +1219,9 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
 }
 
 void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum, ScanQ* sq, int32_t nq,
-                   hipStream_t stream) {
+                   int32_t* h_hits, hipStream_t stream) {
     if (nq <= 0) return;
-    hipLaunchKernelGGL(k_select, dim3(nq), dim3(1024), 0, stream, sample, n, ld, norm_sum, sq);
+    hipLaunchKernelGGL(k_select, dim3(nq), dim3(1024), 0, stream, sample, n, ld, norm_sum, sq, h_hits);
 }
 
 }  // namespace pvs
