@@ -1169,12 +1169,11 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         g_prof.scan_bytes += launches * pass_bytes;
         // kernel variant of the first launch (the only one when nq fits one pass)
         const int first_q = static_cast<int>(std::min<int64_t>(nq, per));
-        int v = mfma ? 8 + (pvs::mfma_tiles_for(first_q) == 1 ? 0 : pvs::mfma_tiles_for(first_q) == 2 ? 1
-                            : pvs::mfma_tiles_for(first_q) == 4 ? 2 : 3)
-                     : first_q - 1;
-        g_prof.variant_ms[v] += t[1];
-        g_prof.variant_launches[v] += launches;
-        g_prof.variant_bytes[v] += launches * pass_bytes;
+        const int tiles = pvs::mfma_tiles_for(v, first_q);
+        const int var = mfma ? 8 + (tiles == 1 ? 0 : tiles == 2 ? 1 : tiles == 4 ? 2 : 3) : first_q - 1;
+        g_prof.variant_ms[var] += t[1];
+        g_prof.variant_launches[var] += launches;
+        g_prof.variant_bytes[var] += launches * pass_bytes;
         g_prof.rescore_ms += t[2];
         g_prof.rescore_rows += kept;
         g_prof.rescore_row_reads += row_reads;

@@ -115,7 +115,7 @@ void launch_scan(const IndexView& ix, const uint64_t* vis, int64_t nblocks, cons
 void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const int8_t* qcodes, const ScanQ* sq, int32_t nq, float gamma, bool sample,
                       const ScanOut& o, void* frag, bool have_frag, hipStream_t stream);
-int mfma_tiles_for(int32_t nq);
+int mfma_tiles_for(const IndexView& ix, int32_t nq);
 
 // tau = the k-th largest selection value of each query's sample, rounded down
 // to a half float (-inf when fewer than k pairs are eligible), into sq; the

@@ -996,14 +996,21 @@ static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
     const uint32_t grid = static_cast<uint32_t>((waves + 3) / 4);
     auto r1 = [&](auto sample_c) {
         constexpr bool S = decltype(sample_c)::value;
-        if constexpr (NQT == 8)   // 256 queries, d = 768: six tiles in LDS, two from L2; d = 384: all in LDS
-            return r1_launch<8, 2, 24, 6, 8, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
-                   r1_launch<8, 0, 12, 6, 8, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream);
+#define PVS_R1(NG, NS, P, W) r1_launch<NQT, NG, NS, P, W, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream)
+        // tiles in L2, K steps, ring depth, wavefronts per workgroup; the
+        // query fragments of d = 1,024 leave no room for eight tiles.  9-32
+        // queries on 1M x 384 take 76 us (5.1 TB/s), on one wavefront per
+        // block 120; 100 queries on 2M x 1,024 389 us (5.3 TB/s), with the
+        // fragments staged per step 581.
+        if constexpr (NQT == 8)   // d = 768: six tiles in LDS, two from L2; d <= 512: all in LDS
+            return PVS_R1(2, 24, 6, 8) || PVS_R1(0, 12, 6, 8) || PVS_R1(0, 16, 4, 8);
         else if constexpr (NQT == 4)
-            return r1_launch<4, 0, 24, 8, 12, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream) ||
-                   r1_launch<4, 0, 12, 6, 12, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream);
+            return PVS_R1(0, 24, 8, 12) || PVS_R1(0, 12, 6, 12) || PVS_R1(0, 32, 8, 8) || PVS_R1(0, 16, 8, 12);
+        else if constexpr (NQT == 2)
+            return PVS_R1(0, 24, 8, 12) || PVS_R1(0, 12, 12, 12) || PVS_R1(0, 32, 8, 12) || PVS_R1(0, 16, 8, 12);
         else
-            return false;
+            return PVS_R1(0, 24, 12, 16) || PVS_R1(0, 12, 12, 16) || PVS_R1(0, 32, 8, 16) || PVS_R1(0, 16, 8, 16);
+#undef PVS_R1
     };
     if (sample ? r1(std::true_type{}) : r1(std::false_type{})) return;
     if (sample) {
@@ -1040,12 +1047,13 @@ static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
     }
 }
 
-// Query tiles of an MFMA pass: one tile up to 32 queries, else the wide
-// kernel with 4 or 8 tiles (33-64 queries also take 4 tiles: the wide
-// kernel streams the codes faster than the two-tile kernel computes).
-int mfma_tiles_for(int32_t nq) {
-    const int t = (nq + 31) / 32;
-    return t <= 1 ? 1 : t <= 4 ? 4 : 8;
+// Query tiles of an MFMA pass: one tile up to 32 queries, two up to 64 where
+// the single-pass kernel has them, else 4 or 8 tiles (the wide kernel streams
+// the codes faster with four tiles than the two-tile kernel computes).
+int mfma_tiles_for(const IndexView& ix, int32_t nq) {
+    const int t = (nq + 31) / 32, ns = ix.nchunk / 2;
+    const bool r1 = ns == 12 || ns == 16 || ns == 24 || ns == 32;
+    return t <= 1 ? 1 : t <= 2 && r1 ? 2 : t <= 4 ? 4 : 8;
 }
 
 void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
@@ -1053,7 +1061,7 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const ScanOut& o, void* frag, bool have_frag, hipStream_t stream) {
     for (int32_t q0 = 0; q0 < nq; q0 += kMaxMfmaQueries) {
         const int32_t n = (nq - q0 < kMaxMfmaQueries) ? (nq - q0) : kMaxMfmaQueries;
-        const int nqt = mfma_tiles_for(n);
+        const int nqt = mfma_tiles_for(ix, n);
         const ScanQ* s = sq + q0;
         if (!have_frag)
             hipLaunchKernelGGL(k_qfrag, dim3((ix.dp / 32) * nqt), dim3(64), 0, stream, qcodes, ix.dp, s,
