@@ -676,9 +676,9 @@ extern "C" int pbm_gpu_open(const pbm_index* ix, const eahr_sparse_query* q, int
         HIP_TRY(hipMemcpyAsync(st->d_qw.p, qw.data(), qw.size() * sizeof(float), hipMemcpyHostToDevice, s));
     }
     EAHR_TRY(grow_dev(st->d_keyoff, std::max<size_t>(1, B) * sizeof(int64_t)));
-    EAHR_TRY(grow_dev(st->d_cnt, 3 * std::max<size_t>(1, B) * sizeof(int32_t)));
+    EAHR_TRY(grow_dev(st->d_cnt, pbmg::kCntLine * std::max<size_t>(1, B) * sizeof(int32_t)));
     EAHR_TRY(grow_pinned(st->h_keyoff, std::max<size_t>(1, B) * sizeof(int64_t)));
-    EAHR_TRY(grow_pinned(st->h_cnt, 3 * std::max<size_t>(1, B) * sizeof(int32_t)));
+    EAHR_TRY(grow_pinned(st->h_cnt, pbmg::kCntLine * std::max<size_t>(1, B) * sizeof(int32_t)));
     // H(R) and the postings count of every (query, range), a chunk of
     // queries per launch; each query's ranges with H > 0 in bound order
     const int64_t nr = ix->n_ranges;
@@ -854,13 +854,13 @@ extern "C" int pbm_gpu_next(pbm_gpu_state* st, const int32_t* m, int64_t* const*
         HIP_TRY(hipMemcpyAsync(st->d_tasks.p, ht, tasks * sizeof(pbmg::Task), hipMemcpyHostToDevice, s));
         HIP_TRY(hipMemcpyAsync(st->d_keyoff.p, hoff, static_cast<size_t>(B) * sizeof(int64_t),
                                hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemsetAsync(dcnt, 0, 3 * static_cast<size_t>(B) * sizeof(int32_t), s));
+        HIP_TRY(hipMemsetAsync(dcnt, 0, pbmg::kCntLine * static_cast<size_t>(B) * sizeof(int32_t), s));
         if (pbmg::launch_expand(v, qv, as<pbmg::Task>(st->d_tasks), static_cast<int32_t>(tasks),
                                 st->ent_ok ? as<int64_t>(st->d_ent) : nullptr, as<int64_t>(st->d_keyoff), dcnt,
-                                dcnt + B, dcnt + 2 * B, as<uint64_t>(st->d_keys), s) != 0)
+                                as<uint64_t>(st->d_keys), s) != 0)
             EAHR_FAIL(EAHR_E_HIP, "pbm_gpu_next: the expansion kernel cannot get %d ids of LDS", ix->range_size);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(st->h_cnt.p, dcnt, 3 * static_cast<size_t>(B) * sizeof(int32_t),
+        HIP_TRY(hipMemcpyAsync(st->h_cnt.p, dcnt, pbmg::kCntLine * static_cast<size_t>(B) * sizeof(int32_t),
                                hipMemcpyDeviceToHost, s));
         if (keys > 0)
             HIP_TRY(hipMemcpyAsync(st->h_keys.p, st->d_keys.p, keys * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
@@ -870,23 +870,22 @@ extern "C" int pbm_gpu_next(pbm_gpu_state* st, const int32_t* m, int64_t* const*
         all_keys += keys;
         t_dev += since(tr);
         tr = std::chrono::steady_clock::now();
-        const int32_t* kc = as<int32_t>(st->h_cnt);
-        const int32_t* sc = kc + B;
-        const int32_t* fl = kc + 2 * B;
+        const int32_t* cnt = as<int32_t>(st->h_cnt);   // keys, scored, failed of each query
         ::eahr::parallel_for(static_cast<int64_t>(round.size()), ::eahr::host_threads(), [&](int64_t i) {
             const int32_t b = round[i];
             pbm_state& S = st->q[b];
             auto& c = st->call[b];
+            const int32_t* C = cnt + static_cast<size_t>(b) * pbmg::kCntLine;
             S.ranges_expanded += static_cast<int64_t>(c.run.size());
             S.postings_visited += static_cast<int64_t>(need[b]);
-            S.items_scored += sc[b];
-            if (fl[b]) {   // a score above its range's bound (App. A.2)
+            S.items_scored += C[1];
+            if (C[2]) {   // a score above its range's bound (App. A.2)
                 S.failed = true;
                 c.n = 0;
                 c.done = true;
             } else {
                 const uint64_t* k = as<uint64_t>(st->h_keys) + hoff[b];
-                S.pool.insert(S.pool.end(), k, k + kc[b]);
+                S.pool.insert(S.pool.end(), k, k + C[0]);
             }
             c.run_pending = false;
         });

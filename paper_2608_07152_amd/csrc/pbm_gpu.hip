@@ -7,7 +7,9 @@
 // values are bit-identical to the host PBM's.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <numeric>
 
 #include "pbm_kernels.h"
 
@@ -69,7 +71,15 @@ __device__ __forceinline__ uint32_t ord32(float f) {
 // Only the bitmap is cleared, so a task costs O(its postings + range / 32).
 // Afterwards each marked document is counted as scored, checked against the
 // bound, and appended as a key when its score is positive: one atomic per
-// wavefront, positions from a wavefront prefix sum of the per-lane counts.
+// wavefront for both counts, positions from a wavefront prefix sum of the
+// per-lane counts.
+//
+// The tasks come query by query; workgroups take them `stride` apart (coprime
+// to their number), so those that run together add to the counters of many
+// queries, which lie a cache line apart: additions to one line are applied one
+// after another.  256 queries over 1M documents (62K tasks, 4.7M postings):
+// 248 us in five launches, 565 with neighbouring tasks and two atomics on
+// neighbouring counters.
 __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
     int x = v;
     for (int off = 1; off < 64; off <<= 1) {
@@ -82,10 +92,11 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
 
 __global__ __launch_bounds__(256) void k_expand(IndexView ix, QueryView q, const Task* __restrict__ tasks,
                                                 const int64_t* __restrict__ ent, const int64_t* __restrict__ key_off,
-                                                int32_t* __restrict__ key_cnt, int32_t* __restrict__ scored,
-                                                int32_t* __restrict__ fail, uint64_t* __restrict__ keys) {
+                                                int32_t* __restrict__ cnt, uint64_t* __restrict__ keys,
+                                                uint32_t stride) {
     extern __shared__ uint32_t smem[];
-    const Task T = tasks[blockIdx.x];
+    const Task T = tasks[static_cast<uint32_t>(static_cast<uint64_t>(blockIdx.x) * stride % gridDim.x)];
+    int32_t* const mine = cnt + static_cast<int64_t>(T.b) * kCntLine;
     const int64_t start = static_cast<int64_t>(T.r) * ix.range_size;
     const int64_t rem = ix.n_docs - start;
     const int32_t len = static_cast<int32_t>(rem < ix.range_size ? rem : ix.range_size);
@@ -124,9 +135,13 @@ __global__ __launch_bounds__(256) void k_expand(IndexView ix, QueryView q, const
         }
         int tot = 0;
         const int at = wave_excl_scan(npos, lane, tot);
+        for (int off = 32; off > 0; off >>= 1) nscored += __shfl_xor(nscored, off, 64);
         int base = 0;
-        if (tot) {
-            if (lane == 0) base = atomicAdd(&key_cnt[T.b], tot);
+        if (nscored) {   // keys in the low half, scored documents (at least as many) in the high
+            if (lane == 0)
+                base = static_cast<int>(atomicAdd(reinterpret_cast<unsigned long long*>(mine),
+                                                  static_cast<unsigned long long>(tot) |
+                                                      static_cast<unsigned long long>(nscored) << 32));
             base = __shfl(base, 0, 64);
             int k = base + at;
             for (uint32_t m = bits; m; m &= m - 1) {
@@ -136,9 +151,7 @@ __global__ __launch_bounds__(256) void k_expand(IndexView ix, QueryView q, const
                     keys[key_off[T.b] + k++] = (static_cast<uint64_t>(~ord32(sc)) << 32) | static_cast<uint64_t>(start + i);
             }
         }
-        for (int off = 32; off > 0; off >>= 1) nscored += __shfl_xor(nscored, off, 64);
-        if (__ballot(bad) && lane == 0) fail[T.b] = 1;
-        if (lane == 0 && nscored) atomicAdd(&scored[T.b], nscored);
+        if (__ballot(bad) && lane == 0) mine[2] = 1;
     }
 }
 
@@ -150,8 +163,7 @@ void launch_bounds(const IndexView& ix, const QueryView& q, float* H, int32_t* p
 }
 
 int launch_expand(const IndexView& ix, const QueryView& q, const Task* tasks, int32_t ntasks,
-                  const int64_t* ent, const int64_t* key_off, int32_t* key_cnt, int32_t* scored,
-                  int32_t* fail, uint64_t* keys, hipStream_t s) {
+                  const int64_t* ent, const int64_t* key_off, int32_t* cnt, uint64_t* keys, hipStream_t s) {
     if (ntasks <= 0) return 0;
     const size_t lds = static_cast<size_t>((ix.range_size + 31) / 32) * sizeof(uint32_t) +
                        static_cast<size_t>(ix.range_size) * sizeof(float);
@@ -160,8 +172,11 @@ int launch_expand(const IndexView& ix, const QueryView& q, const Task* tasks, in
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
         if (e != hipSuccess) return -1;
     }
+    // a stride near the golden section, coprime to the number of tasks
+    uint32_t stride = std::max<uint32_t>(1, static_cast<uint32_t>(0.618 * ntasks));
+    while (std::gcd(stride, static_cast<uint32_t>(ntasks)) != 1) ++stride;
     hipLaunchKernelGGL(k_expand, dim3(static_cast<uint32_t>(ntasks)), dim3(256), lds, s, ix, q, tasks, ent,
-                       key_off, key_cnt, scored, fail, keys);
+                       key_off, cnt, keys, stride);
     return 0;
 }
 

@@ -48,15 +48,20 @@ struct Task {
 void launch_bounds(const IndexView& ix, const QueryView& q, float* H, int32_t* post, int64_t* ent,
                    hipStream_t s);
 
+// Counters of a query during an expansion, a cache line apart: keys appended,
+// documents scored (one 64-bit word), failed.
+constexpr int32_t kCntLine = 32;
+
 // Scores every document of every task's range that carries a term of the
 // task's query (S(x) accumulated like H, in LDS), then for each such
-// document: scored[b] += 1; fail[b] = 1 when S(x) > H(R); and when S(x) > 0
-// its key (~ord(S) << 32 | id) at keys[key_off[b] + atomicAdd(key_cnt[b])].
-// key_off regions must hold the postings of the query's tasks.  ent: the
-// table of launch_bounds for these queries, or null (entries found by
-// binary search).  Returns 0, or -1 when the kernel cannot get its LDS.
+// document: scored += 1; failed = 1 when S(x) > H(R); and when S(x) > 0 its
+// key (~ord(S) << 32 | id) at keys[key_off[b] + j], j counting the query's keys
+// (in no particular order).  cnt: kCntLine ints per query, 8-byte aligned,
+// cleared by the caller.  key_off regions must hold the postings of the
+// query's tasks.  ent: the table of launch_bounds for these queries, or null
+// (entries found by binary search).  Returns 0, or -1 when the kernel cannot
+// get its LDS.
 int launch_expand(const IndexView& ix, const QueryView& q, const Task* tasks, int32_t ntasks,
-                  const int64_t* ent, const int64_t* key_off, int32_t* key_cnt, int32_t* scored,
-                  int32_t* fail, uint64_t* keys, hipStream_t s);
+                  const int64_t* ent, const int64_t* key_off, int32_t* cnt, uint64_t* keys, hipStream_t s);
 
 }  // namespace pbmg
