@@ -633,8 +633,8 @@ __global__ __launch_bounds__(256, 2) void k_scan_mfma_wide(
 
 // ------------------------------------------------ single-pass MFMA scan, LDS queries
 // Query batches of up to 32 NQT queries in one pass over the codes.  A
-// workgroup of W wavefronts per CU (three per SIMD with four tiles, two
-// with eight) holds the query fragments of the first NQT - NG tiles for
+// workgroup of W wavefronts per CU (four per SIMD with one tile, three with
+// two or four, two with eight, or with four tiles of 32 steps) holds the query fragments of the first NQT - NG tiles for
 // every K step in LDS for the whole kernel; the last NG tiles are read from
 // global memory (L2-resident, shared by every workgroup) two steps ahead.
 // Each wavefront takes one 32-row half of a 64-row code block at a time and
