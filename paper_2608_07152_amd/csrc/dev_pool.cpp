@@ -39,10 +39,14 @@ void free_block(const Block& b) {
 
 size_t keep_limit(int where) { return where == kHostSlot ? kKeepHost : kKeepDevice; }
 
-size_t kept_bytes(const Pool& P, int where) {
+size_t kept_bytes(const Pool& P, int where, size_t* blocks) {
     size_t n = 0;
+    *blocks = 0;
     for (const auto& b : P.kept)
-        if (b.where == where) n += b.bytes;
+        if (b.where == where) {
+            n += b.bytes;
+            ++*blocks;
+        }
     return n;
 }
 
@@ -129,11 +133,12 @@ void pool_release(void* p) {
             free_block(b);
             return;
         }
-        size_t n = kept_bytes(P, b.where);
-        for (auto k = P.kept.begin(); k != P.kept.end() && n > keep_limit(b.where);) {
+        size_t blocks = 0, n = kept_bytes(P, b.where, &blocks);
+        for (auto k = P.kept.begin(); k != P.kept.end() && (n > keep_limit(b.where) || blocks > kKeepBlocks);) {
             const auto at = k++;
             if (at->where != b.where) continue;
             n -= at->bytes;
+            --blocks;
             drop.splice(drop.end(), P.kept, at);
         }
     }

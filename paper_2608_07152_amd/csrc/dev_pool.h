@@ -5,7 +5,8 @@
 // of their 0.77 GB take 1.1 ms, and 20 ms once a program frees memory faster
 // than the driver clears it.  Blocks of closed handles are therefore kept for
 // the next ones:
-//  * at most kKeepDevice bytes per GPU and kKeepHost bytes of pinned memory;
+//  * at most kKeepDevice bytes per GPU and kKeepHost bytes of pinned memory,
+//    in at most kKeepBlocks blocks each (requests search them one by one);
 //    past that the blocks kept longest are freed first;
 //  * a kept block that two index releases in a row find unused is freed, so a
 //    program that has moved on to other sizes gets its memory back;
@@ -23,6 +24,7 @@ namespace eahr {
 
 constexpr size_t kKeepDevice = size_t(4) << 30;
 constexpr size_t kKeepHost = size_t(256) << 20;
+constexpr size_t kKeepBlocks = 256;
 
 // At least `bytes` of memory of the current device, or of pinned host memory.
 hipError_t pool_alloc(void** p, size_t bytes, bool host);

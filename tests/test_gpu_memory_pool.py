@@ -86,3 +86,19 @@ def test_memory_is_given_back():
     for _ in range(4):
         E.pvs_free(E.pvs_build(small))
     assert before - torch.cuda.mem_get_info()[0] <= 64 << 20
+
+
+def test_many_states_open_at_once():
+    """More blocks than the pool keeps, closed together and opened again."""
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(2)
+    x = rng.standard_normal((5000, 32)).astype(np.float32)
+    q = rng.standard_normal((3, 32)).astype(np.float32)
+    idx = E.pvs_build(x)
+    want = _want(x, q, 10)
+    for _ in range(2):
+        states = [E.pvs_open(idx, q) for _ in range(150)]
+        for st in states[::10]:
+            assert np.array_equal(E.pvs_next(st, 10)[0], want)
+        for st in states:
+            E.pvs_close(st)
