@@ -834,9 +834,22 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
     const pvs::IndexView v = view_of(ix);
     for (size_t g0 = 0; g0 < todo.size() && n > 0; g0 += static_cast<size_t>(per)) {
         const int32_t ng = static_cast<int32_t>(std::min<int64_t>(per, static_cast<int64_t>(todo.size() - g0)));
-        uint64_t *keys = nullptr, *tmp = nullptr;
-        int32_t *d_qidx = nullptr, *d_cnt = nullptr;
-        ScanQ* d_sq = nullptr;
+        // released on every way out, after what was queued on them has ended
+        struct Buffers {
+            hipStream_t s;
+            bool queued = false;
+            uint64_t *keys = nullptr, *tmp = nullptr;
+            int32_t *qidx = nullptr, *cnt = nullptr;
+            ScanQ* sq = nullptr;
+            ~Buffers() {
+                if (queued) (void)hipStreamSynchronize(s);
+                mem_free(keys);
+                mem_free(tmp);
+                mem_free(qidx);
+                mem_free(cnt);
+                mem_free(sq);
+            }
+        };
         std::vector<int32_t> qidx(ng), cnt(ng, static_cast<int32_t>(n));
         std::vector<ScanQ> sq(ng);
         for (int32_t i = 0; i < ng; ++i) {
@@ -845,21 +858,22 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
             sq[i].qi = qidx[i];
             sq[i].cand_off = static_cast<int64_t>(i) * n;
         }
-        int rc = EAHR_OK;
-        auto body = [&]() -> int {
-            EAHR_TRY(dev_alloc(&keys, static_cast<size_t>(ng) * n));
-            EAHR_TRY(dev_alloc(&tmp, static_cast<size_t>(ng) * n));
-            EAHR_TRY(dev_alloc(&d_qidx, ng));
-            EAHR_TRY(dev_alloc(&d_cnt, ng));
-            EAHR_TRY(dev_alloc(&d_sq, ng));
-            HIP_TRY(hipMemcpyAsync(d_qidx, qidx.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync(d_cnt, cnt.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync(d_sq, sq.data(), ng * sizeof(ScanQ), hipMemcpyHostToDevice, s));
+        {
+            Buffers d{s};
+            EAHR_TRY(dev_alloc(&d.keys, static_cast<size_t>(ng) * n));
+            EAHR_TRY(dev_alloc(&d.tmp, static_cast<size_t>(ng) * n));
+            EAHR_TRY(dev_alloc(&d.qidx, ng));
+            EAHR_TRY(dev_alloc(&d.cnt, ng));
+            EAHR_TRY(dev_alloc(&d.sq, ng));
+            d.queued = true;
+            HIP_TRY(hipMemcpyAsync(d.qidx, qidx.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, s));
+            HIP_TRY(hipMemcpyAsync(d.cnt, cnt.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, s));
+            HIP_TRY(hipMemcpyAsync(d.sq, sq.data(), ng * sizeof(ScanQ), hipMemcpyHostToDevice, s));
             if (prof) HIP_TRY(hipEventRecord(st->ev[0], s));
-            pvs::launch_full_keys(v, st->vis, n, st->qrows, d_qidx, ng, keys, n, s);
+            pvs::launch_full_keys(v, st->vis, n, st->qrows, d.qidx, ng, d.keys, n, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[1], s));
-            const uint64_t* sorted = pvs::launch_segmented_sort(keys, tmp, d_cnt, 1, d_sq, ng, n, nullptr, s);
+            const uint64_t* sorted = pvs::launch_segmented_sort(d.keys, d.tmp, d.cnt, 1, d.sq, ng, n, nullptr, s);
             HIP_TRY(hipGetLastError());
             if (prof) HIP_TRY(hipEventRecord(st->ev[2], s));
             for (int32_t i = 0; i < ng; ++i) {
@@ -870,15 +884,8 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
                                            st->n_vis * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
             }
             HIP_TRY(hipStreamSynchronize(s));
-            return EAHR_OK;
-        };
-        rc = body();
-        mem_free(keys);
-        mem_free(tmp);
-        mem_free(d_qidx);
-        mem_free(d_cnt);
-        mem_free(d_sq);
-        if (rc != EAHR_OK) return rc;
+            d.queued = false;
+        }
         if (prof) {
             float t0 = 0.0f, t1 = 0.0f;
             HIP_TRY(hipEventElapsedTime(&t0, st->ev[0], st->ev[1]));
