@@ -834,15 +834,20 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
     const pvs::IndexView v = view_of(ix);
     for (size_t g0 = 0; g0 < todo.size() && n > 0; g0 += static_cast<size_t>(per)) {
         const int32_t ng = static_cast<int32_t>(std::min<int64_t>(per, static_cast<int64_t>(todo.size() - g0)));
-        // released on every way out, after what was queued on them has ended
+        // released on every way out, after what was queued on them has ended;
+        // a group that did not complete leaves no ranks behind
         struct Buffers {
-            hipStream_t s;
+            pvs_state* st;
+            const std::vector<int32_t>& group;
             bool queued = false;
             uint64_t *keys = nullptr, *tmp = nullptr;
             int32_t *qidx = nullptr, *cnt = nullptr;
             ScanQ* sq = nullptr;
             ~Buffers() {
-                if (queued) (void)hipStreamSynchronize(s);
+                if (queued) {
+                    (void)hipStreamSynchronize(st->ix->stream);
+                    for (int32_t b : group) st->q[b].cache.clear();
+                }
                 mem_free(keys);
                 mem_free(tmp);
                 mem_free(qidx);
@@ -859,7 +864,7 @@ static int full_scan_round(pvs_state* st, std::vector<int32_t>& todo) {
             sq[i].cand_off = static_cast<int64_t>(i) * n;
         }
         {
-            Buffers d{s};
+            Buffers d{st, qidx};
             EAHR_TRY(dev_alloc(&d.keys, static_cast<size_t>(ng) * n));
             EAHR_TRY(dev_alloc(&d.tmp, static_cast<size_t>(ng) * n));
             EAHR_TRY(dev_alloc(&d.qidx, ng));

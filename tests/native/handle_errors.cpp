@@ -150,7 +150,12 @@ int client(int32_t generator, int step, long fail, long* calls) {
         done(pvs_next(st, kM, nullptr, ids.data(), scores.data(), cnt.data(), sts.data()));
         arm();   // again: after a failure from the same place, else from the cache
         if (done(pvs_next(st, kM, nullptr, ids.data(), scores.data(), cnt.data(), sts.data())))
-            for (int32_t b = 0; b < kB; ++b) fake::expect(cnt[b] == kM, "a later read is short");
+            for (int32_t b = 0; b < kB; ++b) {
+                fake::expect(cnt[b] == kM, "a later read is short");
+                const int64_t first = failed ? 0 : kM;
+                for (int32_t i = 0; i < kM; ++i)
+                    fake::expect(ids[b * kM + i] == first + i, "a later read is not the next ranks");
+            }
         pvs_close(st);
     } else {
         at += 2;
