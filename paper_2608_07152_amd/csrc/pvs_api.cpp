@@ -502,6 +502,8 @@ static int ensure_query_buffers(pvs_state* st, int32_t nq, int64_t sample_ld) {
     mem_free(st->qfrag);
     mem_free(st->h_scanq);
     mem_free(st->h_counts);
+    st->buf_nq = 0;   // until all of them are there
+    st->buf_sample = 0;
     EAHR_TRY(dev_alloc(&st->scanq, nq));
     EAHR_TRY(dev_alloc(&st->counts, all_counts(nq)));
     EAHR_TRY(dev_alloc(&st->sample, static_cast<size_t>(nq) * sample_ld));

@@ -140,9 +140,9 @@ int client(int32_t generator, int step, long fail, long* calls) {
     pvs_index* ix = nullptr;
     arm();
     if (!done(pvs_build(rows.data(), 100, kDim, EAHR_PTR_HOST, nullptr, &ix))) return failed;
-    std::vector<int64_t> ids(kB * kM);
-    std::vector<float> scores(kB * kM);
-    std::vector<int32_t> cnt(kB), sts(kB);
+    std::vector<int64_t> ids(20 * kM);
+    std::vector<float> scores(20 * kM);
+    std::vector<int32_t> cnt(20), sts(20);
     pvs_state* st = nullptr;
     arm();
     if (done(pvs_open_gen(ix, 0, rows.data(), kB, EAHR_PTR_HOST, generator, &st))) {
@@ -159,6 +159,19 @@ int client(int32_t generator, int step, long fail, long* calls) {
         pvs_close(st);
     } else {
         at += 2;
+    }
+    // a wider batch grows the buffers that the index keeps; after a growth that
+    // failed, a batch of the old size must not find them missing
+    for (int32_t wide : {20, kB}) {
+        st = nullptr;
+        arm();
+        if (done(pvs_open_gen(ix, 0, rows.data(), wide, EAHR_PTR_HOST, generator, &st))) {
+            arm();
+            done(pvs_next(st, kM, nullptr, ids.data(), scores.data(), cnt.data(), sts.data()));
+            pvs_close(st);
+        } else {
+            at += 1;
+        }
     }
     arm();
     pvs::g_rows = 200;
@@ -177,7 +190,7 @@ int main() {
     for (int32_t generator : {EAHR_GEN_INTERVALS, EAHR_GEN_FULL_SCAN}) {
         long n = 0;
         fake::expect(client(generator, -1, -1, &n) == 0, "the program fails by itself");
-        for (int step = 0; step < 6; ++step)
+        for (int step = 0; step < 10; ++step)
             for (long fail = 0;; ++fail) {
                 n = 0;
                 const int failed = client(generator, step, fail, &n);
