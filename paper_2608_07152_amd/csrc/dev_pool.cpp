@@ -128,7 +128,8 @@ void pool_release(void* p) {
         const Block b = it->second;
         P.live.erase(it);
         try {
-            P.kept.push_back(b);
+            // a block above the limit goes by itself and takes no other with it
+            (b.bytes > keep_limit(b.where) ? drop : P.kept).push_back(b);
         } catch (...) {
             free_block(b);
             return;

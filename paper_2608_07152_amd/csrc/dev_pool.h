@@ -7,7 +7,8 @@
 // the next ones:
 //  * at most kKeepDevice bytes per GPU and kKeepHost bytes of pinned memory,
 //    in at most kKeepBlocks blocks each (requests search them one by one);
-//    past that the blocks kept longest are freed first;
+//    past that the blocks kept longest are freed first; a block larger than
+//    the limit is freed at once;
 //  * a kept block that two index releases in a row find unused is freed, so a
 //    program that has moved on to other sizes gets its memory back;
 //  * when an allocation fails, every kept block of that kind is freed and the

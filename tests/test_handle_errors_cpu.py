@@ -26,3 +26,7 @@ def _run(tmp_path, test, sources):
 
 def test_a_failing_call_releases_no_busy_memory(tmp_path):
     _run(tmp_path, "handle_errors.cpp", ["pvs_api.cpp", "errors.cpp"])
+
+
+def test_rules_of_the_memory_pool(tmp_path):
+    _run(tmp_path, "dev_pool_rules.cpp", ["dev_pool.cpp"])
