@@ -117,7 +117,7 @@ hipError_t pool_alloc(void** p, size_t bytes, bool host) {
     }
 }
 
-void pool_release(void* p) {
+static void release(void* p, bool keep) {
     if (!p) return;
     Pool& P = pool();
     std::list<Block> drop;
@@ -129,7 +129,7 @@ void pool_release(void* p) {
         P.live.erase(it);
         try {
             // a block above the limit goes by itself and takes no other with it
-            (b.bytes > keep_limit(b.where) ? drop : P.kept).push_back(b);
+            (keep && b.bytes <= keep_limit(b.where) ? P.kept : drop).push_back(b);
         } catch (...) {
             free_block(b);
             return;
@@ -145,6 +145,9 @@ void pool_release(void* p) {
     }
     for (const auto& b : drop) free_block(b);
 }
+
+void pool_release(void* p) { release(p, true); }
+void pool_free(void* p) { release(p, false); }
 
 void pool_age() {
     Pool& P = pool();

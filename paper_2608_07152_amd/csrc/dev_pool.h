@@ -31,6 +31,8 @@ constexpr size_t kKeepBlocks = 256;
 hipError_t pool_alloc(void** p, size_t bytes, bool host);
 // Back to the pool (null is allowed).  The block must be idle.
 void pool_release(void* p);
+// Freed, not kept: for memory that no later request will match.
+void pool_free(void* p);
 // An index has been released: kept blocks that were already unused at the
 // previous release are freed.
 void pool_age();

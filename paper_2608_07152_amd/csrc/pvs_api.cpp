@@ -145,12 +145,10 @@ static int index_grow(pvs_index* ix, int64_t need_rows) {
         HIP_TRY(hipMemcpyAsync(live, ix->live, ix->cap / 64 * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
     }
-    mem_free(ix->codes);
-    mem_free(ix->scale);
-    mem_free(ix->vnorm);
-    mem_free(ix->enorm);
-    mem_free(ix->frows);
-    mem_free(ix->live);
+    // freed, not kept for others: the next growth asks for half as much again
+    for (void* p : {static_cast<void*>(ix->codes), static_cast<void*>(ix->scale), static_cast<void*>(ix->vnorm),
+                    static_cast<void*>(ix->enorm), static_cast<void*>(ix->frows), static_cast<void*>(ix->live)})
+        ::eahr::pool_free(p);
     ix->codes = codes;
     ix->scale = scale;
     ix->vnorm = vnorm;

@@ -30,3 +30,7 @@ def test_a_failing_call_releases_no_busy_memory(tmp_path):
 
 def test_rules_of_the_memory_pool(tmp_path):
     _run(tmp_path, "dev_pool_rules.cpp", ["dev_pool.cpp"])
+
+
+def test_memory_that_a_long_lived_index_holds(tmp_path):
+    _run(tmp_path, "handle_memory.cpp", ["pvs_api.cpp", "dev_pool.cpp", "errors.cpp"])
