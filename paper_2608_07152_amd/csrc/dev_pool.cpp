@@ -1,6 +1,7 @@
 #include "dev_pool.h"
 
 #include <algorithm>
+#include <cstdint>
 #include <list>
 #include <mutex>
 #include <new>
@@ -15,14 +16,15 @@ constexpr int kHostSlot = -1;   // "device" of pinned host memory
 struct Block {
     void* p;
     size_t bytes;
-    int where;      // device, or kHostSlot
-    int ages = 0;   // index releases it has been kept through
+    int where;          // device, or kHostSlot
+    uint64_t since = 0;   // the clock when it was released
 };
 
 struct Pool {
     std::mutex mu;
     std::unordered_map<void*, Block> live;   // handed out
     std::list<Block> kept;                   // oldest first
+    uint64_t clock = 0;
 };
 
 // Never destroyed: handles may be closed while the process ends, after the
@@ -79,8 +81,7 @@ hipError_t pool_alloc(void** p, size_t bytes, bool host) {
                     (best == P.kept.end() || it->bytes < best->bytes))
                     best = it;
             if (best != P.kept.end()) {
-                Block b = *best;
-                b.ages = 0;
+                const Block b = *best;
                 P.live.emplace(b.p, b);
                 P.kept.erase(best);
                 *p = b.p;
@@ -125,7 +126,8 @@ static void release(void* p, bool keep) {
         std::lock_guard<std::mutex> lk(P.mu);
         const auto it = P.live.find(p);
         if (it == P.live.end()) return;
-        const Block b = it->second;
+        Block b = it->second;
+        b.since = P.clock;
         P.live.erase(it);
         try {
             // a block above the limit goes by itself and takes no other with it
@@ -149,15 +151,14 @@ static void release(void* p, bool keep) {
 void pool_release(void* p) { release(p, true); }
 void pool_free(void* p) { release(p, false); }
 
-void pool_age() {
+void pool_age(int ticks) {
     Pool& P = pool();
     std::list<Block> drop;
     {
         std::lock_guard<std::mutex> lk(P.mu);
-        for (auto it = P.kept.begin(); it != P.kept.end();) {
-            const auto at = it++;
-            if (++at->ages > 2) drop.splice(drop.end(), P.kept, at);
-        }
+        P.clock += static_cast<uint64_t>(ticks);
+        while (!P.kept.empty() && P.clock - P.kept.front().since >= kKeepTicks)
+            drop.splice(drop.end(), P.kept, P.kept.begin());
     }
     for (const auto& b : drop) free_block(b);
 }

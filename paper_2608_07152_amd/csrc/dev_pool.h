@@ -9,8 +9,9 @@
 //    in at most kKeepBlocks blocks each (requests search them one by one);
 //    past that the blocks kept longest are freed first; a block larger than
 //    the limit is freed at once;
-//  * a kept block that two index releases in a row find unused is freed, so a
-//    program that has moved on to other sizes gets its memory back;
+//  * a kept block that no request has taken since the second index release
+//    after its own, or for kKeepTicks closed states, is freed, so a program
+//    that has moved on to other sizes gets its memory back;
 //  * when an allocation fails, every kept block of that kind is freed and the
 //    allocation tried again.
 // Any thread may call; the lock is held across the bookkeeping only.  A block
@@ -33,8 +34,11 @@ hipError_t pool_alloc(void** p, size_t bytes, bool host);
 void pool_release(void* p);
 // Freed, not kept: for memory that no later request will match.
 void pool_free(void* p);
-// An index has been released: kept blocks that were already unused at the
-// previous release are freed.
-void pool_age();
+// A handle has been closed: the pool's clock goes on by `ticks`, and kept blocks
+// that have been unused for kKeepTicks are freed.
+constexpr int kKeepTicks = 96;
+constexpr int kTicksIndex = kKeepTicks / 3;
+constexpr int kTicksState = 1;
+void pool_age(int ticks);
 
 }  // namespace eahr

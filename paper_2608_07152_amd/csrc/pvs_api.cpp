@@ -112,7 +112,7 @@ pvs_index::~pvs_index() {
     mem_free(staging);
     for (auto& s : snaps) mem_free(s.vis);
     free_buffers(spare);
-    ::eahr::pool_age();
+    ::eahr::pool_age(::eahr::kTicksIndex);
 }
 
 static int index_grow(pvs_index* ix, int64_t need_rows) {
@@ -647,6 +647,7 @@ extern "C" void pvs_close(pvs_state* st) {
         }
     }
     delete st;
+    ::eahr::pool_age(::eahr::kTicksState);
     if (!ix) return;
     bool release = false;
     {

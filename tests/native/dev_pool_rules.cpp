@@ -32,10 +32,35 @@ void oversized() {
     fake::expect(fake::in_use[1] == kKeepHost, "the pool is not filled to its limit");
 }
 
+// A block nobody asks for again goes at the third index release counting its
+// own owner's, or after kKeepTicks closed states; one in use in turn stays.
+void ages() {
+    pool_age(kKeepTicks);
+    fake::expect(fake::in_use[0] == 0 && fake::in_use[1] == 0, "old blocks stay");
+    pool_release(take(kMiB));
+    for (int i = 0; i < 2; ++i) pool_age(kTicksIndex);
+    fake::expect(fake::in_use[0] == kMiB, "a block goes at the second index release");
+    pool_age(kTicksIndex);
+    fake::expect(fake::in_use[0] == 0, "a block outlives the third index release");
+    void* other = take(3 * kMiB);
+    pool_release(take(kMiB));
+    for (int i = 0; i < kKeepTicks - 1; ++i) pool_age(kTicksState);
+    pool_release(other);
+    fake::expect(fake::in_use[0] == 5 * kMiB, "a block goes early");   // 3 MiB round up to 4
+    pool_age(kTicksState);
+    fake::expect(fake::in_use[0] == 4 * kMiB, "not only the old block goes");
+    for (int i = 0; i < 4 * kKeepTicks; ++i) {   // taken now and then
+        if (i % 64 == 0) pool_release(take(3 * kMiB));
+        pool_age(kTicksState);
+        fake::expect(fake::frees[0] == 2 && fake::in_use[0] == 4 * kMiB, "a block in use in turn goes");
+    }
+}
+
 }  // namespace
 
 int main() {
     oversized();
+    ages();
     std::printf("ok\n");
     return 0;
 }

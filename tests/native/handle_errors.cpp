@@ -18,7 +18,7 @@ void pool_release(void* p) {
     fake::release(p, fake::blocks.at(static_cast<char*>(p)).second);
 }
 void pool_free(void* p) { pool_release(p); }
-void pool_age() {}
+void pool_age(int) {}
 }  // namespace eahr
 
 namespace {

@@ -21,6 +21,16 @@ pvs_index* build(const std::vector<float>& rows, int64_t n) {
     return ix;
 }
 
+void read(pvs_index* ix, const std::vector<float>& rows, int32_t B) {
+    pvs_state* st = nullptr;
+    std::vector<int64_t> ids(B);
+    std::vector<float> sc(B);
+    std::vector<int32_t> cnt(B), sts(B);
+    fake::expect(pvs_open(ix, 0, rows.data(), B, EAHR_PTR_HOST, &st) == EAHR_OK, "open");
+    fake::expect(pvs_next(st, 1, nullptr, ids.data(), sc.data(), cnt.data(), sts.data()) == EAHR_OK, "next");
+    pvs_close(st);
+}
+
 // An index that grows by inserts keeps its arrays and nothing of the smaller ones.
 void growth() {
     const int64_t step = 20000;
@@ -37,10 +47,26 @@ void growth() {
     pvs_free(ix);
 }
 
+// Reads that no longer need a large batch's buffers give them back in the end.
+void closes() {
+    const std::vector<float> rows(8192 * kDim, 1.0f);
+    pvs_index* ix = build(rows, 100);
+    read(ix, rows, 8);
+    const size_t before = held();
+    for (int wide = 0; wide < 2; ++wide) read(ix, rows, 8192);   // its query rows, codes and pinned copies
+    const size_t spare = held();
+    for (int i = 0; i < 200; ++i) read(ix, rows, 8);
+    // what the index keeps for its next state stays, the closed states' own memory goes
+    fake::expect(held() <= spare - 8192 * kDim * 4, "memory of closed states is held for ever");
+    fake::expect(held() >= before, "a block in use was freed");
+    pvs_free(ix);
+}
+
 }  // namespace
 
 int main() {
     growth();
+    closes();
     std::printf("ok\n");
     return 0;
 }
