@@ -92,15 +92,7 @@ hipError_t pool_alloc(void** p, size_t bytes, bool host) {
         hipError_t e = raw_alloc(&q, bytes, host);
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
-            std::list<Block> drop;
-            {
-                std::lock_guard<std::mutex> lk(P.mu);
-                for (auto it = P.kept.begin(); it != P.kept.end();) {
-                    const auto at = it++;
-                    if (at->where == where) drop.splice(drop.end(), P.kept, at);
-                }
-            }
-            for (const auto& b : drop) free_block(b);
+            pool_trim(host);
             e = raw_alloc(&q, bytes, host);
         }
         if (e != hipSuccess) return e;
@@ -150,6 +142,21 @@ static void release(void* p, bool keep) {
 
 void pool_release(void* p) { release(p, true); }
 void pool_free(void* p) { release(p, false); }
+
+void pool_trim(bool host) {
+    int where = kHostSlot;
+    if (!host && hipGetDevice(&where) != hipSuccess) return;
+    Pool& P = pool();
+    std::list<Block> drop;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        for (auto it = P.kept.begin(); it != P.kept.end();) {
+            const auto at = it++;
+            if (at->where == where) drop.splice(drop.end(), P.kept, at);
+        }
+    }
+    for (const auto& b : drop) free_block(b);
+}
 
 void pool_age(int ticks) {
     Pool& P = pool();

@@ -34,6 +34,9 @@ hipError_t pool_alloc(void** p, size_t bytes, bool host);
 void pool_release(void* p);
 // Freed, not kept: for memory that no later request will match.
 void pool_free(void* p);
+// Frees the kept blocks of the current device, or the pinned ones: for callers
+// whose own allocation has failed.
+void pool_trim(bool host);
 // A handle has been closed: the pool's clock goes on by `ticks`, and kept blocks
 // that have been unused for kKeepTicks are freed.
 constexpr int kKeepTicks = 96;

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "common.h"
+#include "dev_pool.h"
 #include "eahr.h"
 #include "host_parallel.h"
 #include "pbm_internal.h"
@@ -462,11 +463,24 @@ extern "C" void pbm_close(pbm_state* st) {
 
 namespace {
 
+// Device or pinned host memory; when there is none, what the pool of closed
+// handles only keeps is freed first.
+hipError_t alloc(void** p, size_t bytes, bool host) {
+    auto get = [&]() { return host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes); };
+    hipError_t e = get();
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        ::eahr::pool_trim(host);
+        e = get();
+    }
+    return e;
+}
+
 template <class T>
 int dev_alloc_n(T** p, size_t n) {
     *p = nullptr;
     if (n == 0) n = 1;
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(p), n * sizeof(T)));
+    HIP_TRY(alloc(reinterpret_cast<void**>(p), n * sizeof(T), false));
     return EAHR_OK;
 }
 
@@ -581,7 +595,7 @@ int grow_dev(pbm_buf& b, size_t bytes) {
     if (b.p) HIP_TRY(hipFree(b.p));
     b.p = nullptr;
     b.cap = 0;
-    HIP_TRY(hipMalloc(&b.p, cap));
+    HIP_TRY(alloc(&b.p, cap, false));
     b.cap = cap;
     return EAHR_OK;
 }
@@ -592,7 +606,7 @@ int grow_pinned(pbm_buf& b, size_t bytes) {
     if (b.p) HIP_TRY(hipHostFree(b.p));
     b.p = nullptr;
     b.cap = 0;
-    HIP_TRY(hipHostMalloc(&b.p, cap, hipHostMallocDefault));
+    HIP_TRY(alloc(&b.p, cap, true));
     b.cap = cap;
     return EAHR_OK;
 }

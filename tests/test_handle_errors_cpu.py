@@ -34,3 +34,7 @@ def test_rules_of_the_memory_pool(tmp_path):
 
 def test_memory_that_a_long_lived_index_holds(tmp_path):
     _run(tmp_path, "handle_memory.cpp", ["pvs_api.cpp", "dev_pool.cpp", "errors.cpp"])
+
+
+def test_sparse_channel_beside_kept_memory(tmp_path):
+    _run(tmp_path, "sparse_memory.cpp", ["pbm.cpp", "dev_pool.cpp", "errors.cpp"])
