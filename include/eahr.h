@@ -226,6 +226,12 @@ int pvs_scores_noalloc(const pvs_state* st, int32_t b, const int64_t* rows, int6
 void pvs_close(pvs_state* st);
 void pvs_free(pvs_index* idx);
 
+/* Closed dense states and indexes leave memory for the next ones: at most
+ * 4 GiB per GPU and 256 MiB of pinned host memory, given back when later
+ * handles leave it unused.  eahr_release_memory frees all of it now, for a
+ * program whose other allocations need it; open handles are not affected. */
+void eahr_release_memory(void);
+
 /* ------------------------------------------- hierarchical merging (dense) */
 
 /* Hierarchical merging of exact dense rankings (Sec. 2.4).  A Segment is a

@@ -1,5 +1,7 @@
 #include "dev_pool.h"
 
+#include "eahr.h"
+
 #include <algorithm>
 #include <cstdint>
 #include <list>
@@ -171,3 +173,13 @@ void pool_age(int ticks) {
 }
 
 }  // namespace eahr
+
+extern "C" void eahr_release_memory(void) {
+    eahr::Pool& P = eahr::pool();
+    std::list<eahr::Block> drop;
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        drop.swap(P.kept);
+    }
+    for (const auto& b : drop) eahr::free_block(b);
+}

@@ -129,6 +129,7 @@ SIGNATURES = {
     "pvs_scores_noalloc": (C.c_int, [_P, _i32, _i64p, _i64, _f32p]),
     "pvs_close": (None, [_P]),
     "pvs_free": (None, [_P]),
+    "eahr_release_memory": (None, []),
     "pbm_build": (C.c_int, [_i64p, _i32, _i32p, _f32p, _i64, _i32, C.POINTER(_P)]),
     "pbm_free": (None, [_P]),
     "pbm_open": (C.c_int, [_P, C.POINTER(eahr_sparse_query), C.POINTER(_P)]),
@@ -517,6 +518,12 @@ def pvs_close(state: PvsState) -> None:
 
 def pvs_free(index: PvsIndex) -> None:
     index.free()
+
+
+def eahr_release_memory() -> None:
+    """Frees the device and pinned memory that closed handles left for the next
+    ones; open handles are not affected."""
+    load().eahr_release_memory()
 
 
 # ------------------------------------------------------------------ sparse

@@ -2,6 +2,7 @@
 #include "hip_fake.h"
 
 #include "dev_pool.h"
+#include "eahr.h"
 
 using namespace eahr;
 
@@ -56,11 +57,25 @@ void ages() {
     }
 }
 
+// The public call frees what is kept and nothing that is in use.
+void given_back() {
+    void *p = take(kMiB), *h = take(kMiB, true);
+    pool_release(take(2 * kMiB));
+    pool_release(take(2 * kMiB, true));
+    eahr_release_memory();
+    fake::expect(fake::in_use[0] == kMiB && fake::in_use[1] == kMiB, "kept blocks stay, or one in use goes");
+    pool_release(p);
+    pool_release(h);
+    eahr_release_memory();
+    fake::expect(fake::in_use[0] == 0 && fake::in_use[1] == 0, "memory is held after the call");
+}
+
 }  // namespace
 
 int main() {
     oversized();
     ages();
+    given_back();
     std::printf("ok\n");
     return 0;
 }

@@ -102,3 +102,29 @@ def test_many_states_open_at_once():
             assert np.array_equal(E.pvs_next(st, 10)[0], want)
         for st in states:
             E.pvs_close(st)
+
+
+def test_release_memory():
+    """What closed handles left is free after the call; open handles go on."""
+    import torch
+    from paper_2608_07152_amd import eahr as E
+    q = np.ones((1, 256), np.float32)
+    _first_ids(E, np.ones((64, 256), np.float32), q, 5)
+    E.eahr_release_memory()
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((3000, 256)).astype(np.float32)
+    held = E.pvs_build(x)
+    st = E.pvs_open(held, x[:2])
+    first = E.pvs_next(st, 10)[0]
+    before = torch.cuda.mem_get_info()[0]
+    big = torch.ones(1_000_000, 256, device="cuda")
+    E.pvs_free(E.pvs_build(big))                # 1.3 GB kept
+    del big
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] > 1 << 30
+    E.eahr_release_memory()
+    assert before - torch.cuda.mem_get_info()[0] <= 64 << 20
+    ids = np.concatenate([first, E.pvs_next(st, 40)[0]], axis=1)
+    assert np.array_equal(ids, _want(x, x[:2], 50))
+    E.pvs_close(st)
+    E.pvs_free(held)
