@@ -124,28 +124,57 @@ __device__ __forceinline__ float scaled_threshold(float thr, float sq) {
     return (r > -INFINITY && r < INFINITY) ? r : -INFINITY;
 }
 
-// A sampled pair is kept as two half floats: the value tau is selected from
-// (lower bound or midpoint) in the low half, the upper bound in the high one,
-// both times a power of two of the query that puts the largest score bound of
-// the index just below 2^15, and rounded towards zero.  So the halves order
-// like the values, to 2^-10 relative (the guard term alone makes an interval
-// wider than that), and a value is never below its half when that is >= 0.
-// Pairs that are not eligible hold -inf twice.
-constexpr uint32_t kSampleNone = 0xfc00fc00u;
+// A sampled pair is kept as two 16-bit codes: the value tau is selected from
+// (lower bound or midpoint) in the low half, the upper bound in the high one.
+// A code is the value over a power of two of the query that puts the largest
+// score bound of the index just below 1, rounded towards zero: from 2^-14 on a
+// half float (2^-10 relative), below that a bfloat16 (2^-7 relative, down to
+// the smallest float32), so that one row of a huge norm does not flatten the
+// scores of the others.  The half floats' codes are moved up to follow on the
+// bfloat16's, so codes order like the values, and a value is never below its
+// code's when that is >= 0.  tau only decides how much is rescored.  Pairs
+// that are not eligible hold kSampleNone, which is no value's code.
+constexpr uint32_t kSampleNone = 0xffffffffu;
+constexpr uint32_t kSampleTiny = 0x3880;        // the code of 2^-14
+constexpr uint32_t kSampleShift = kSampleTiny - 0x0400;   // minus its half float
+constexpr uint32_t kSampleOne = 0x3c00 + kSampleShift;    // the code of 1
 
+__device__ __forceinline__ float pow2f(int e) { return __uint_as_float(static_cast<uint32_t>(127 + e) << 23); }
+// 2^this is above every score bound of the query (as long as that is a float).
 template <typename QF>
 __device__ __forceinline__ int sample_exp(const QF& Q, float norm_sum) {
-    const float L = Q.nqh * norm_sum + Q.wmax;   // at least wmax > 0
-    return static_cast<int>(__float_as_uint(L) >> 23) - 127;
+    const float L = Q.nqh * norm_sum + Q.wmax;   // at least wmax > 0; may overflow
+    const int e = static_cast<int>((__float_as_uint(L) >> 23) & 0xff) - 126;
+    return e < 126 ? e : 126;
 }
-__device__ __forceinline__ float pow2f(int e) { return __uint_as_float(static_cast<uint32_t>(127 + e) << 23); }
 
 __device__ __forceinline__ uint32_t sample_pack(float lo, float hi, bool midpoint, float scale) {
-    const float v = midpoint ? 0.5f * lo + 0.5f * hi : lo;
-    const auto h = __builtin_amdgcn_cvt_pkrtz(v * scale, hi * scale);
+    // infinite bounds (and NaN) to the ends of the codes' range
+    const float a = __builtin_amdgcn_fmed3f((midpoint ? 0.5f * lo + 0.5f * hi : lo) * scale, -8.0f, 8.0f);
+    const float b = __builtin_amdgcn_fmed3f(hi * scale, -8.0f, 8.0f);
+    const auto h = __builtin_amdgcn_cvt_pkrtz(a, b);
     uint32_t r;
     __builtin_memcpy(&r, &h, 4);
-    return r;
+    r += kSampleShift * 0x10001u;   // at most 8: no carry into the sign
+    const uint32_t x = fabsf(a) < 0x1p-14f ? __float_as_uint(a) >> 16 : r & 0xffffu;
+    const uint32_t y = fabsf(b) < 0x1p-14f ? __float_as_uint(b) & 0xffff0000u : r & 0xffff0000u;
+    return x | y;
+}
+// Codes in the order of their values, from 0 (the least) to 0xffff.
+__device__ __forceinline__ int sample_order(uint32_t code) {
+    return static_cast<int>((code & 0x8000u) ? (~code & 0xffffu) : (code | 0x8000u));
+}
+// The value of the code with order o, times 2^e.
+__device__ __forceinline__ float sample_value(int o, int e) {
+    const uint32_t m = static_cast<uint32_t>(o >= 0x8000 ? o : ~o) & 0x7fffu;
+    float f = __uint_as_float(m << 16);
+    if (m >= kSampleTiny) {
+        const uint16_t b16 = static_cast<uint16_t>(m - kSampleShift);
+        _Float16 h;
+        __builtin_memcpy(&h, &b16, 2);
+        f = static_cast<float>(h);
+    }
+    return (o >= 0x8000 ? f : -f) * pow2f(e);
 }
 
 // Sum of the 16 lanes of every row of the wavefront as a pairwise tree:

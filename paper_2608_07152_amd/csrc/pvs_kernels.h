@@ -74,7 +74,7 @@ void launch_quantize(const float* src, int64_t nrows, int32_t d, int64_t src_str
 // Largest |x| of count floats into flags[3] (float bits), non-finite into flags[0].
 void launch_maxabs(const float* src, int64_t count, uint32_t* flags, hipStream_t stream);
 
-// Outputs of a scan pass.  Sample pass: two half floats (sample_pack) of every
+// Outputs of a scan pass.  Sample pass: two 16-bit codes (sample_pack) of every
 // (query, row) pair of the sampled blocks, row-major [query][sample_ld].
 // Main pass: every candidate pair (hi >= tau)
 // becomes one record (row, index of the query in the scan, exact integer dot
@@ -118,7 +118,7 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
 int mfma_tiles_for(const IndexView& ix, int32_t nq);
 
 // tau = the k-th largest selection value of each query's sample, rounded down
-// to a half float (-inf when fewer than k pairs are eligible), into sq; the
+// to a sample code's value (-inf when fewer than k pairs are eligible), into sq; the
 // number of sampled pairs of query b with hi >= tau to h_hits[b] (pinned).
 void launch_select(const uint32_t* sample, int64_t n, int64_t ld, float norm_sum, ScanQ* sq, int32_t nq,
                    int32_t* h_hits, hipStream_t stream);

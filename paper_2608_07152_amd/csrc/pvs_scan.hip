@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void k_scan_gemv(
         pair_interval(Q, sv, nv, nev, acc[b], gamma, lo, hi);
         const bool elig = visible && (!Q.has_cert || lo <= Q.s_cert);
         if (SAMPLE) {
-            const float scale = pow2f(14 - sample_exp(Q, o.norm_sum));
+            const float scale = pow2f(-sample_exp(Q, o.norm_sum));
             o.sample[b * o.sample_ld + w * 64 + lane] =
                 elig ? sample_pack(lo, hi, o.sample_mid != 0, scale) : kSampleNone;
         } else if (elig && hi >= Q.tau) {
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void k_scan_mfma(
         if (SAMPLE) {
             // a lane's four consecutive rows go out in one store
             if (!valid) continue;
-            const float scale = pow2f(14 - sample_exp(Q, o.norm_sum));
+            const float scale = pow2f(-sample_exp(Q, o.norm_sum));
             uint32_t* dst = o.sample + b * o.sample_ld + w * 64 + 4 * (lane >> 5);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
                 Q.nq = f.nq;
                 Q.nqh = f.nqh;
                 Q.neq = f.neq;
-                const float scl = pow2f(14 - sample_exp(f, o.norm_sum));
+                const float scl = pow2f(-sample_exp(f, o.norm_sum));
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
                     uint32_t x[4];
@@ -1085,25 +1085,21 @@ void launch_scan_mfma(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
 }
 
 // ------------------------------------------------------------ threshold
-// tau = the k-th largest selection value of a query's sample, to the half
-// float it is kept as, and the number of sampled pairs with hi >= tau.
+// tau = the k-th largest selection value of a query's sample, to the code it
+// is kept as, and the number of sampled pairs with hi >= tau.
 //
-// One pass over the sample counts both halves of every pair in two LDS
-// histograms, one bin per half float, over a window of 8,192 of them: eight
-// octaves below the largest score bound, which hold the k-th value unless it
-// is below 1/256 of that bound (then the next windows down follow, each with
-// its own pass).  A suffix sum finds the bin.  One workgroup per query, bound
-// by the latency of its loads: 8.8M x 768 (137K samples a query), 28 us for
-// one query, 33 us for 256; the earlier kernel, up to six radix passes over
-// two floats a pair, took 120 and 247 us.  Up to sixteen workgroups per query
-// that added their bins to a global histogram took 67 to 150 us: the atomics
-// cost more than the pass they split.
+// One pass over the sample counts both codes of every pair in two LDS
+// histograms, one bin per code, over a window of 8,192 of them: eight octaves
+// below the largest score bound, which hold the k-th value unless it is below
+// 1/256 of that bound (then the next windows down follow, each with its own
+// pass).  A suffix sum finds the bin.  One workgroup per query, bound by the
+// latency of its loads: 8.8M x 768 (137K samples a query), 28 us for one
+// query, 33 us for 256; up to six radix passes over two floats a pair took 120
+// and 247 us.  Up to sixteen workgroups per query that added their bins to a
+// global histogram took 67 to 150 us: the atomics cost more than the pass they
+// split.
 constexpr int kBins = 8192;
-constexpr int kSelTop = 0xf800;   // order of the half float 2^15, above every kept value
-
-__device__ __forceinline__ int half_order(uint32_t h) {
-    return static_cast<int>((h & 0x8000u) ? (~h & 0xffffu) : (h | 0x8000u));
-}
+constexpr int kSelTop = 0x8000 + kSampleOne;   // above every value's order
 
 __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sample, int64_t n,
                                                  int64_t ld, float norm_sum, ScanQ* __restrict__ sq,
@@ -1136,12 +1132,12 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
                 const uint32_t w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if ((w4[e] & 0xffffu) == 0xfc00u) continue;   // not eligible
+                    if (w4[e] == kSampleNone) continue;   // not eligible
                     ++elig;
 #pragma unroll
                     for (int z = 0; z < 2; ++z) {
-                        const int c = half_order(z ? w4[e] >> 16 : w4[e] & 0xffffu) - base;
-                        // at or above the first window's top: rounding only
+                        const int c = sample_order(z ? w4[e] >> 16 : w4[e] & 0xffffu) - base;
+                        // above the first window's top: infinite bounds only
                         if (c >= 0 && (c < kBins || win == 0)) atomicAdd(&bins[z][c < kBins ? c : kBins - 1], 1u);
                     }
                 }
@@ -1200,22 +1196,17 @@ __global__ __launch_bounds__(1024) void k_select(const uint32_t* __restrict__ sa
             if (bin >= 8 * tid && bin < 8 * tid + 8) {
                 uint32_t hits = above[1] + suf[1] - own[1];
                 for (int i = 7; i >= bin - 8 * tid; --i) hits += bins[1][8 * tid + i];
-                // the largest value at most the bin's: its half float, or for a
-                // negative one (rounded up) the half float below
+                // the largest code's value at most the bin's values: its own, or
+                // for a negative one (rounded up) the next code's below
                 const int c = base + bin;
-                const int h = c >= 0x8000 ? c : c - 1;
-                const uint32_t bits = static_cast<uint32_t>(h >= 0x8000 ? h & 0x7fff : ~h & 0xffff);
-                _Float16 f;
-                const uint16_t b16 = static_cast<uint16_t>(bits);
-                __builtin_memcpy(&f, &b16, 2);
-                sq[b].tau = static_cast<float>(f) * pow2f(sample_exp(Q, norm_sum) - 14);
+                sq[b].tau = sample_value(c >= 0x8000 ? c : c - 1, sample_exp(Q, norm_sum));
                 h_hits[b] = static_cast<int32_t>(hits);
             }
             return;
         }
         above[0] += all[0];
         above[1] += all[1];
-        if (base <= 0) {   // cannot happen (k <= total): every half float has been counted
+        if (base <= 0) {   // cannot happen (k <= total): every code has been counted
             if (tid == 0) {
                 sq[b].tau = -INFINITY;
                 h_hits[b] = static_cast<int32_t>(total);

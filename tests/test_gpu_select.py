@@ -1,7 +1,8 @@
-"""Threshold selection from the sample (half-float histogram windows): the
+"""Threshold selection from the sample (histogram windows over 16-bit codes): the
 prefix stays exact and the scans stay selective where the k-th value lies in
-the first window, far below it (one row of a huge norm), below zero (every
-score negative), at zero, and where every value is the same; for the
+the first window, far below it (one row of a huge norm, also where the codes
+are bfloat16's), below zero (every score negative), at zero, and where every
+value is the same; for the
 one-query, small-batch, one-, four- and eight-tile sample passes and for
 samples of every block (small n) and of some (large n)."""
 import numpy as np
@@ -10,7 +11,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _check(E, x, q, m, max_candidates=None):
+def _check(E, x, q, m, max_candidates):
     idx = E.pvs_build(x)
     st = E.pvs_open(idx, q)
     ids, sc, cnt, _ = E.pvs_next(st, m)
@@ -22,13 +23,12 @@ def _check(E, x, q, m, max_candidates=None):
         assert np.array_equal(ids[b], want)
         assert np.array_equal(sc[b] + 0.0, s[want] + 0.0)
     st_ = E.pvs_stats(st)
-    if max_candidates is not None:
-        assert st_["candidates"] <= max_candidates * len(q), st_
+    assert st_["candidates"] <= max_candidates * len(q), st_
 
 
 @pytest.mark.parametrize("n,d,B", [(5000, 48, 1), (5000, 48, 20), (300_001, 16, 1), (300_001, 16, 7),
                                    (290_000, 64, 40), (270_000, 384, 40), (270_000, 384, 200), (262_144, 64, 140)])
-@pytest.mark.parametrize("kind", ["plain", "outlier", "negative", "zero", "same"])
+@pytest.mark.parametrize("kind", ["plain", "outlier", "sentinel", "tiny", "negative", "zero", "same"])
 def test_selected_threshold(n, d, B, kind):
     from paper_2608_07152_amd import eahr as E
     rng = np.random.default_rng(n + d + B)
@@ -36,20 +36,30 @@ def test_selected_threshold(n, d, B, kind):
     x /= np.linalg.norm(x, axis=1, keepdims=True)
     q = rng.standard_normal((B, d), dtype=np.float32)
     q /= np.linalg.norm(q, axis=1, keepdims=True)
-    m, limit = 300, None
+    m = 300
+    # the first scan certifies the request or min(2^17, n / 16) ranks over its
+    # queries, 1.25 times or five standard deviations above that, and the widest
+    # intervals here (d = 384) reach 2.5 times as many rows: at most 4.4 times
+    # the larger of the two in all
+    limit = 6 * max(m, min(1 << 17, n // 16) // B)
     if kind == "outlier":
         x[n // 2] *= 1e4       # the k-th score is below 1e-4 of the index's largest bound
+    elif kind == "sentinel":
+        x[n // 2] *= 1e15
+    elif kind == "tiny":
+        x *= 1e-12
+        x[n // 2] *= 1e27
     elif kind == "negative":
         x = np.abs(x)
         q = -np.abs(q)
+        limit *= 4             # wider intervals: the scores are larger than their spread
     elif kind == "zero":
+        limit = n
         x[:, 0] = 0
         x[: n - 50, :] = 0     # nearly every score is exactly 0
     elif kind == "same":
         x[:] = x[0]
-        m = 40
-    if kind in ("plain", "outlier") and n > 200_000 and d == 64:
-        limit = n // 2
+        m, limit = 40, 7 * n   # every scan takes them all
     _check(E, x, q, m, limit)
 
 
@@ -60,4 +70,4 @@ def test_selection_scale_extremes():
     for rs, qs in ((1e-18, 1e-18), (1e18, 1e15), (1e-30, 1.0), (1e15, 1e-30)):
         x = (rng.standard_normal((6000, 32)) * rs).astype(np.float32)
         q = (rng.standard_normal((3, 32)) * qs).astype(np.float32)
-        _check(E, x, q, 200)
+        _check(E, x, q, 200, 6 * (6000 // 16))
