@@ -637,9 +637,9 @@ extern "C" void pvs_close(pvs_state* st) {
     const pvs_index* ix = st->ix;
     if (ix) {
         (void)hipStreamSynchronize(ix->stream);
-        if (!st->expected && st->calls > 0) {
+        if (!st->expected && st->stats.scans > 0) {
             const int had = ix->read_on.load(std::memory_order_relaxed);
-            ix->read_on.store(st->calls > 1 ? 2 : std::max(0, had - 1), std::memory_order_relaxed);
+            ix->read_on.store(st->read_past ? 2 : std::max(0, had - 1), std::memory_order_relaxed);
         }
         if (!ix->has_spare) {
             donate_buffers(st, ix->spare);
@@ -965,6 +965,7 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
                             ? ahead / nq
                             : std::max({factor * (Q.emitted + m), pvs::kSpecFloor, floor_all / nq}) - have;
         const int64_t spec = st->spec_off ? 0 : std::min(depth, pvs::kSpecBudget / nq);
+        if (Q.scans == 0) Q.shallow = std::max({need, mmin, std::min(ahead, pvs::kSpecBudget) / nq});
         const int64_t overlap = lower_overlap(st, b);
         const int64_t target = std::max({need, mmin, spec}) + overlap;
         const double nf = static_cast<double>(need + overlap) * frac;
@@ -1253,14 +1254,16 @@ static int next_ranks(pvs_state* st, int32_t m, const uint8_t* active, int64_t* 
                       int32_t* count, int32_t* status) {
     const int32_t B = st->B;
     std::vector<int32_t> todo;
-    st->calls += m > 0;
     for (int32_t b = 0; b < B; ++b) {
         if (active && !active[b]) continue;
         auto& Q = st->q[b];
         if (Q.retired) EAHR_FAIL(EAHR_E_INVALID, "pvs_next: query %d was retired", b);
-        if (Q.failed || Q.cert_exhausted) continue;
         const int64_t avail = certified_count(Q) - Q.emitted;
-        if (avail < m) todo.push_back(b);
+        const bool served = Q.failed || Q.cert_exhausted || avail >= m;
+        // does it ask for more than a shallow first scan certified, or would have?
+        if (Q.scans > 0 && std::min(Q.emitted + m, st->n_vis) > Q.shallow && (st->reads_on || !served))
+            st->read_past = true;
+        if (!served) todo.push_back(b);
     }
     for (int guard = 0; !todo.empty(); ++guard) {
         if (guard > 200) EAHR_FAIL(EAHR_E_HIP, "pvs_next: scan loop did not converge");

@@ -64,8 +64,10 @@ constexpr int64_t kTargetBudget = 8192;
 // another scan.  So the first scan of a state certifies the request and about
 // min(2^17, rows / 16) ranks ahead over its queries (rescoring them costs at
 // most about an eighth of streaming the codes), unless its caller always
-// reads on (eahr_topk, merges: pvs_expect_depth) or the last states closed on
-// the index did; the second scan takes kSpecSecond in place of the factor.
+// reads on (eahr_topk, merges: pvs_expect_depth) or one of the last two states
+// closed on the index read past what such a scan certifies (by ranks, not by
+// calls: short pages served by one scan do not count); the second scan takes
+// kSpecSecond in place of the factor.
 // Certified 16 requests ahead at once, 256 queries for 1,000 ranks on
 // 1M x 384 took 3,010 us and 256 for 100 on 8.8M x 768 4,950; as now 980 and
 // 2,910.  Never predicting that a caller reads on made 4 of 12 paging
@@ -170,8 +172,8 @@ struct pvs_index {
     std::vector<Snapshot> snaps;
     mutable ScanBuffers spare;   // buffers of the last closed state
     mutable bool has_spare = false;
-    // whether the states closed last read on past their first request: 2
-    // after one that did, one less after each that did not
+    // whether the states closed last read past what a shallow first scan
+    // certifies: 2 after one that did, one less after each that did not
     mutable std::atomic<int> read_on{0};
     // states opened on the index and not closed yet; pvs_free while some are
     // open only marks the index, and the last pvs_close releases it
@@ -199,6 +201,7 @@ struct pvs_state {
         bool cert_exhausted = false;    // every visible row certified
         int retries = 0;                // consecutive scans that certified too few
         int scans = 0;                  // scans that certified ranks for it
+        int64_t shallow = 0;            // ranks that a shallow first scan aims at
         int64_t cap_hint = 0;           // candidate capacity needed by the last overflow
         int64_t evals = 0;              // (query, row) pairs rescored in float32
     };
@@ -229,7 +232,7 @@ struct pvs_state {
     bool spec_off = false;             // scans certify no further ahead than asked
     bool reads_on = false;             // the first scan certifies as far ahead as later ones
     bool expected = false;             // its caller said so (pvs_expect_depth)
-    int64_t calls = 0;                 // pvs_next calls that asked for ranks
+    bool read_past = false;            // was asked for more than a shallow first scan certifies
     // test knob: first-attempt key regions and pool divided by this, so that
     // the overflow and rescan paths run (results do not change)
     int64_t cap_shrink = 1;

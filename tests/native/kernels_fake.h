@@ -1,5 +1,6 @@
 // Stand-ins for the dense channel's kernels on the CPU: they check that their
-// buffers are live and large enough, and rank the rows of an index by id.
+// buffers are live and large enough, and rank the rows of an index by id.  A
+// scan certifies every row, or with g_by_k the next k rows of each query.
 #pragma once
 #include <cstring>
 #include <initializer_list>
@@ -13,6 +14,12 @@ namespace pvs {
 // every visible row scores 0: keys in id order
 static uint64_t key_of(int64_t row) { return (static_cast<uint64_t>(~0x80000000u) << 32) | static_cast<uint64_t>(row); }
 static int64_t g_rows = 0;
+static bool g_by_k = false;
+static int64_t first_of(const ScanQ& q) { return g_by_k && q.has_cert ? q.id_cert + 1 : 0; }
+static int64_t count_of(const ScanQ& q) {
+    const int64_t left = g_rows - first_of(q);
+    return g_by_k && q.k < left ? q.k : left;
+}
 static void queued(std::initializer_list<std::pair<const void*, size_t>> bufs) {
     for (const auto& b : bufs) fake::expect(fake::inside(b.first, b.second), "a kernel was given a bad buffer");
     fake::busy = true;
@@ -62,10 +69,10 @@ void launch_scan_report(const int32_t*, int64_t, int32_t*, const int32_t*, int32
     std::memset(hp, 0, kSub * 4);
     std::memset(he, 0, nq * 4);
 }
-void launch_cert_report(int32_t*, const int32_t*, const ScanQ*, int32_t nq, int32_t* hc, int32_t* hf, hipStream_t) {
-    queued({{hc, nq * 4}, {hf, nq * 4}});
+void launch_cert_report(int32_t*, const int32_t*, const ScanQ* sq, int32_t nq, int32_t* hc, int32_t* hf, hipStream_t) {
+    queued({{sq, nq * sizeof(ScanQ)}, {hc, nq * 4}, {hf, nq * 4}});
     for (int32_t i = 0; i < nq; ++i) {
-        hc[i] = static_cast<int32_t>(g_rows);
+        hc[i] = static_cast<int32_t>(count_of(sq[i]));
         hf[i] = 0;
     }
 }
@@ -88,10 +95,12 @@ uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t*, i
                                 uint64_t* packed, hipStream_t) {
     queued({{keys, max * 8}, {tmp, max * 8}, {sq, nq * sizeof(ScanQ)}});
     if (!packed) return keys;
-    queued({{packed, nq * max * 8}});
+    int64_t n = 0;
+    for (int32_t i = 0; i < nq; ++i) n += count_of(sq[i]);
+    queued({{packed, n * 8}});
     for (int32_t i = 0; i < nq; ++i)
-        for (int64_t r = 0; r < max; ++r) packed[i * max + r] = key_of(r);
-    return packed;
+        for (int64_t r = 0; r < count_of(sq[i]); ++r) *packed++ = key_of(first_of(sq[i]) + r);
+    return packed - n;
 }
 void launch_intervals(const IndexView&, const int8_t*, const ScanQ*, float, const int64_t* r, int64_t n, float* lo, float* hi,
                       hipStream_t) {

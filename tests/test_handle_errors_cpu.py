@@ -38,3 +38,7 @@ def test_memory_that_a_long_lived_index_holds(tmp_path):
 
 def test_sparse_channel_beside_kept_memory(tmp_path):
     _run(tmp_path, "sparse_memory.cpp", ["pbm.cpp", "dev_pool.cpp", "errors.cpp"])
+
+
+def test_how_far_ahead_scans_certify(tmp_path):
+    _run(tmp_path, "reading_on.cpp", ["pvs_api.cpp", "dev_pool.cpp", "errors.cpp"])
