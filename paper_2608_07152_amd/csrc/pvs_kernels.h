@@ -135,7 +135,8 @@ void launch_regions(const ScanQ* h_sq, ScanQ* sq, int32_t nq, hipStream_t stream
 void launch_scan_report(const int32_t* pair_cnt, int64_t pair_sub, int32_t* cbase, const int32_t* q_evals,
                         int32_t nq, int32_t* h_pcnt, int32_t* h_evals, hipStream_t stream);
 // After rescoring: to the host each query's count of certified keys and its
-// failure; the device's count is cut to the query's key region.
+// failure; the device's count is cut to the query's key region, and where the
+// query's keys start when they are packed goes into the count's line.
 void launch_cert_report(int32_t* cert_cnt, const int32_t* fail, const ScanQ* sq, int32_t nq,
                         int32_t* h_cert, int32_t* h_fail, hipStream_t stream);
 
@@ -170,8 +171,9 @@ void launch_full_keys(const IndexView& ix, const uint64_t* vis, int64_t n_rows, 
 // Sorts every query's candidate keys (cnt[b * cnt_ld] keys from cand_off) ascending;
 // returns the buffer holding the result: keys or tmp (each query's keys from
 // its cand_off), or, when given, packed, with the queries' keys one after
-// another.  packed may be pinned host memory: only the last kernel writes it,
-// and nothing reads it.
+// another (cnt as launch_cert_report leaves it, cnt_ld = kCertStride).  packed
+// may be pinned host memory: only the last kernel writes it, and nothing reads
+// it.
 uint64_t* launch_segmented_sort(uint64_t* keys, uint64_t* tmp, const int32_t* cnt, int32_t cnt_ld,
                                 const ScanQ* sq, int32_t nq, int64_t max_cnt, uint64_t* packed,
                                 hipStream_t stream);

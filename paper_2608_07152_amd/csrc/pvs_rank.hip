@@ -83,16 +83,47 @@ void launch_scan_report(const int32_t* pair_cnt, int64_t pair_sub, int32_t* cbas
                        cbase, q_evals, nq, h_pcnt, h_evals);
 }
 
+// Where the keys of query i start when the queries' keys lie one after another.
+__device__ __forceinline__ int64_t* packed_offset(int32_t* cnt, int i) {
+    return reinterpret_cast<int64_t*>(cnt + static_cast<int64_t>(i) * kCertStride + 2);
+}
+__device__ __forceinline__ int64_t packed_offset(const int32_t* cnt, int i) {
+    return *reinterpret_cast<const int64_t*>(cnt + static_cast<int64_t>(i) * kCertStride + 2);
+}
+
+// One thread per query; a workgroup adds up the counts of the queries before
+// its own for the offsets, once: each workgroup of the sort did it for itself
+// before, which grows with the square of the batch.
 __global__ __launch_bounds__(256) void k_cert_report(int32_t* __restrict__ cert_cnt, const int32_t* __restrict__ fail,
                                                      const ScanQ* __restrict__ sq, int32_t nq,
                                                      int32_t* __restrict__ h_cert, int32_t* __restrict__ h_fail) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    __shared__ int64_t s_before[4], s_own[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int first = blockIdx.x * 256, i = first + tid;
+    // (another workgroup may have cut a count already: the same value again)
+    auto kept = [&](int j, int32_t c) { return min(static_cast<int64_t>(c), kSub * sq[j].cand_cap); };
+    int64_t before = 0;
+    for (int j = tid; j < first; j += 256) before += kept(j, cert_cnt[j * kCertStride]);
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    const int32_t c = i < nq ? cert_cnt[i * kCertStride] : 0;
+    const int64_t own = i < nq ? kept(i, c) : 0;
+    int64_t upto = own;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t y = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += y;
+    }
+    if (lane == 63) {
+        s_before[wave] = before;
+        s_own[wave] = upto;
+    }
+    __syncthreads();
     if (i >= nq) return;
-    const int32_t c = cert_cnt[i * kCertStride];
+    int64_t at = upto - own;
+    for (int w = 0; w < 4; ++w) at += s_before[w] + (w < wave ? s_own[w] : 0);
     h_cert[i] = c;
     h_fail[i] = fail[i];
-    const int64_t region = kSub * sq[i].cand_cap;
-    if (c > region) cert_cnt[i * kCertStride] = static_cast<int32_t>(region);
+    if (c > own) cert_cnt[i * kCertStride] = static_cast<int32_t>(own);
+    *packed_offset(cert_cnt, i) = at;
 }
 
 void launch_cert_report(int32_t* cert_cnt, const int32_t* fail, const ScanQ* sq, int32_t nq,
@@ -347,21 +378,6 @@ void launch_rescore(const IndexView& ix, const float* qrows, const ScanQ* sq, in
 #undef PVS_RS
 }
 
-// Where query b's keys start when the queries' keys lie one after another:
-// the sum of the counts before it, taken by the whole workgroup.
-__device__ __forceinline__ int64_t packed_offset(const int32_t* __restrict__ cnt, int cnt_ld, int b) {
-    __shared__ int64_t part[16];
-    const int waves = static_cast<int>(blockDim.x >> 6), wave = static_cast<int>(threadIdx.x >> 6);
-    int64_t x = 0;
-    for (int i = threadIdx.x; i < b; i += blockDim.x) x += cnt[i * cnt_ld];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    if ((threadIdx.x & 63) == 0) part[wave] = x;
-    __syncthreads();
-    x = 0;
-    for (int w = 0; w < waves; ++w) x += part[w];
-    return x;
-}
-
 // ------------------------------------------------------------------ sorting
 // Ascending sort of every tile of 512 WAVES keys of every query's region.
 // Keys past the region's count are padded with ~0 (no real key: a row id is
@@ -442,7 +458,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_sort_tiles(const uint64_t* __res
     if (base >= n) return;
     const int m = static_cast<int>(min(static_cast<int64_t>(T), n - base));
     const uint64_t* k = keys + sq[b].cand_off + base;
-    uint64_t* d = dst + (packed ? packed_offset(cnt, cnt_ld, b) : sq[b].cand_off) + base;
+    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off) + base;
     uint64_t v[PER];
     // any assignment of the unsorted keys to threads will do: the coalesced one
 #pragma unroll
@@ -535,7 +551,7 @@ __global__ __launch_bounds__(256) void k_merge(const uint64_t* __restrict__ src,
     if (o0 >= n) return;
     const int64_t o1 = min(o0 + T, n);
     const uint64_t* s = src + sq[b].cand_off;
-    uint64_t* d = dst + (packed ? packed_offset(cnt, cnt_ld, b) : sq[b].cand_off);
+    uint64_t* d = dst + (packed ? packed_offset(cnt, b) : sq[b].cand_off);
     const int64_t start = (o0 / (2 * run)) * (2 * run);
     const int64_t mid = min(start + run, n);
     const int64_t end = min(start + 2 * run, n);

@@ -47,3 +47,22 @@ def test_lists_of_different_lengths_pack_next_to_each_other():
     for b in range(len(q)):
         s = E.pvs_scores(st, b, rows).astype(np.float64)
         assert np.array_equal(got[b], np.lexsort((rows, -s))[:got.shape[1]])
+
+
+@pytest.mark.parametrize("B", [256, 257, 1000])
+def test_large_batches_pack(B):
+    """More queries than one workgroup of the offsets takes, their lists of
+    different lengths."""
+    from paper_2608_07152_amd import eahr as E
+    rng = np.random.default_rng(B)
+    n, d = 6000, 8
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    x[: n // 2] *= 0.1
+    q = rng.standard_normal((B, d)).astype(np.float32)
+    idx = E.pvs_build(x)
+    st = E.pvs_open(idx, q)
+    got = np.concatenate([E.pvs_next(st, m)[0] for m in (3, 700)], axis=1)
+    rows = np.arange(n)
+    for b in list(range(0, B, 17)) + [255, B - 1]:
+        s = E.pvs_scores(st, b, rows).astype(np.float64)
+        assert np.array_equal(got[b], np.lexsort((rows, -s))[:got.shape[1]]), b
