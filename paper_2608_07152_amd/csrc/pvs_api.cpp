@@ -944,9 +944,9 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         return EAHR_OK;
     }
     const int64_t stride = std::max<int64_t>(1, nblocks / pvs::kSampleBlocks);
-    const int64_t nsb = (nblocks + stride - 1) / stride;
-    const int64_t sample_ld = nsb * 64;
-    const double frac = static_cast<double>(nsb) / static_cast<double>(nblocks);
+    const int64_t sample_ld = pvs::sample_blocks(nblocks, stride) * 64;
+    const double frac = static_cast<double>(pvs::sample_runs(nblocks, stride) * pvs::kSampleRun) /
+                        static_cast<double>(nblocks * 64);
     EAHR_TRY(ensure_query_buffers(st, nq, sample_ld));
 
     const int64_t ahead = std::min(pvs::kSpecFloorBudget, st->n_rows / 16);   // ranks ahead that a scan pays for
@@ -971,7 +971,8 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         const double nf = static_cast<double>(need + overlap) * frac;
         double k = (stride == 1) ? static_cast<double>(target)
                                  : std::ceil(std::max(pvs::kSampleMargin * target * frac,
-                                                      nf + pvs::kSampleSigmas * std::sqrt(nf) + 4.0));
+                                                      nf + pvs::kSampleSigmas * std::sqrt(pvs::kSampleRun * nf) +
+                                                          1.5 * pvs::kSampleRun));
         for (int r = 0; r < Q.retries; ++r) k *= 4.0;
         sq.k = static_cast<int32_t>(std::min(k, 2.0e9));
         st->h_scanq[i] = sq;

@@ -16,17 +16,20 @@
 using KeyCache = std::vector<uint64_t, ::eahr::NoInit<uint64_t>>;
 
 namespace pvs {
-// Threshold estimation samples every stride-th code block, with the largest
-// stride that keeps at least this many blocks sampled.
+// Threshold estimation samples every stride-th run of kSampleRun rows, with the
+// largest stride that keeps at least this many blocks' worth of rows sampled.
 // With stride 1 tau is the target-th largest lower bound, so at least the
 // target is certified.  With a larger stride tau is taken from the sampled
 // interval midpoints (close to the scores, so the rows certified, s >= tau,
 // number about the target scaled by the stride) with this relative margin.
 constexpr int64_t kSampleBlocks = 2048;
-// The request itself is certified with five standard deviations of its count
-// in the sample, because falling short costs another scan.
+// The request itself is certified with a margin on its count in the sample,
+// because falling short costs another scan.  Its rows may lie side by side, so
+// they are taken to fall into the sample by whole runs: four standard deviations
+// of a Poisson count of runs and one and a half runs more, which one query in
+// 10,000 exceeds where every run is full, and fewer anywhere else.
 constexpr double kSampleMargin = 1.25;
-constexpr double kSampleSigmas = 5.0;
+constexpr double kSampleSigmas = 4.0;
 // Smallest candidate pool allocated for a scan, and the largest pool one scan
 // round may use (queries beyond it wait for the next round).
 constexpr int64_t kMinCap = 4096;

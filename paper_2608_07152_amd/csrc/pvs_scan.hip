@@ -2,8 +2,8 @@
 // Int8 codes are streamed once per scan; each (query, row) pair gets its exact
 // integer dot product and its score interval (pvs_device.h), and rows whose
 // interval can reach the query's threshold tau are appended to the query's
-// candidate region.  A sample pass over every sample_stride-th block records
-// the bounds from which tau is selected.
+// candidate region.  A sample pass over every sample_stride-th run of rows
+// records the bounds from which tau is selected.
 //
 // Two kernels compute the same integers: a dot4 GEMV for a few queries and an
 // Int8 MFMA contraction for batches.
@@ -25,16 +25,21 @@ template <int QB, bool SAMPLE>
 __global__ __launch_bounds__(256) void k_scan_gemv(
     const uint4* __restrict__ codes, const float* __restrict__ scale,
     const float* __restrict__ vnorm, const float* __restrict__ enorm,
-    const uint64_t* __restrict__ vis, int64_t nblocks, int32_t nchunk,
+    const uint64_t* __restrict__ vis, int64_t nblocks, int64_t nwaves, int32_t nchunk,
     const int8_t* __restrict__ qcodes, int32_t dp, const ScanQ* __restrict__ sq, float gamma,
     ScanOut o) {
     const int lane = threadIdx.x & 63;
     const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    const int64_t blk = SAMPLE ? w * o.sample_stride : w;
-    if (blk >= nblocks) return;
-    const int64_t row = blk * 64 + lane;
-    const uint64_t vbits = vis[blk];
-    const bool visible = (vbits >> lane) & 1ull;
+    if (w >= nwaves) return;
+    int64_t row = w * 64 + lane;
+    bool there = true;
+    if constexpr (SAMPLE) {
+        row = sample_row(row, o.sample_stride);
+        there = row < nblocks * 64;
+        if (!there) row = 0;
+    }
+    const int64_t blk = SAMPLE ? row >> 6 : w;
+    const bool visible = there && ((vis[blk] >> (row & 63)) & 1ull);
     const float sv = scale[row];
     const float nv = vnorm[row];
     const float nev = enorm[row];
@@ -46,7 +51,7 @@ __global__ __launch_bounds__(256) void k_scan_gemv(
     int acc[QB];
 #pragma unroll
     for (int b = 0; b < QB; ++b) acc[b] = 0;
-    const uint4* cp = codes + blk * nchunk * 64 + lane;
+    const uint4* cp = codes + blk * nchunk * 64 + (row & 63);
 #pragma unroll 4
     for (int c = 0; c < nchunk; ++c) {
         const u32x4 x = load_nt(cp + c * 64);
@@ -112,15 +117,15 @@ template <int QB>
 static void gemv_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                       const int8_t* qcodes, const ScanQ* sq, float gamma, bool sample,
                       const ScanOut& o, hipStream_t stream) {
-    const int64_t waves = sample ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks;
+    const int64_t waves = sample ? sample_blocks(nblocks, o.sample_stride) : nblocks;
     const uint32_t grid = static_cast<uint32_t>((waves + 3) / 4);
     if (sample) {
         hipLaunchKernelGGL((k_scan_gemv<QB, true>), dim3(grid), dim3(256), 0, stream, ix.codes,
-                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qcodes, ix.dp,
+                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, waves, ix.nchunk, qcodes, ix.dp,
                            sq, gamma, o);
     } else {
         hipLaunchKernelGGL((k_scan_gemv<QB, false>), dim3(grid), dim3(256), 0, stream, ix.codes,
-                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qcodes, ix.dp,
+                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, waves, ix.nchunk, qcodes, ix.dp,
                            sq, gamma, o);
     }
 }
@@ -313,9 +318,9 @@ __global__ __launch_bounds__(64) void k_qfrag(const int8_t* __restrict__ qcodes,
     frag[(static_cast<int64_t>(s) * nqt + u) * 64 + lane] = v;
 }
 
-// One wavefront per 64-row block and NQT tiles of 32 queries, processed NQS
-// tiles at a time (2 x NQS accumulators of 32 x 32; a second half re-reads
-// the block's codes from L2).  Epilogue per query tile: lane l owns query
+// One wavefront per 64-row block (or 64 positions of the sample) and NQT tiles
+// of 32 queries, processed NQS tiles at a time (2 x NQS accumulators of
+// 32 x 32; a second half re-reads the block's codes from L2).  Epilogue per query tile: lane l owns query
 // 32 u + l % 32 and 32 of the block's rows; the centre-score pre-test skips
 // the exact interval for rows that cannot reach tau; survivors of lanes l and
 // l ^ 32 (same query) become records through emit_pairs.
@@ -323,15 +328,27 @@ template <int NQT, bool SAMPLE>
 __global__ __launch_bounds__(256) void k_scan_mfma(
     const uint4* __restrict__ codes, const float* __restrict__ scale,
     const float* __restrict__ vnorm, const float* __restrict__ enorm,
-    const uint64_t* __restrict__ vis, int64_t nblocks, int32_t nchunk,
+    const uint64_t* __restrict__ vis, int64_t nblocks, int64_t nwaves, int32_t nchunk,
     const v4i* __restrict__ qfrag, const ScanQ* __restrict__ sq, int32_t nq, float gamma,
     ScanOut o) {
     constexpr int NQS = NQT < 4 ? NQT : 4;
     const int lane = threadIdx.x & 63;
     const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    const int64_t blk = SAMPLE ? w * o.sample_stride : w;
-    if (blk >= nblocks) return;
-    const uint64_t vbits = vis[blk];
+    if (w >= nwaves) return;
+    const int64_t blk = w;
+    // the row at position i of the wavefront's 64 (row 0 where there is none)
+    auto row_at = [&](int i) {
+        if constexpr (!SAMPLE) return w * 64 + i;
+        const int64_t r = sample_row(w * 64 + i, o.sample_stride);
+        return r < nblocks * 64 ? r : int64_t(0);
+    };
+    uint64_t vbits;
+    if constexpr (SAMPLE) {
+        const int64_t r = row_at(lane);
+        vbits = __ballot(sample_row(w * 64 + lane, o.sample_stride) < nblocks * 64 && ((vis[r >> 6] >> (r & 63)) & 1ull));
+    } else {
+        vbits = vis[blk];
+    }
     // scale and norms of this lane's 32 rows, loaded before the K loop so the
     // epilogue's interval tests never wait on memory
     float svr[2][16], vnr[2][16], enr[2][16];
@@ -339,12 +356,14 @@ __global__ __launch_bounds__(256) void k_scan_mfma(
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int64_t row = blk * 64 + 32 * t + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            const int64_t row = row_at(32 * t + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
             svr[t][r] = scale[row];
             vnr[t][r] = vnorm[row];
             enr[t][r] = enorm[row];
         }
-    const uint4* A = codes + blk * nchunk * 64 + (lane >> 5) * 64 + (lane & 31);
+    const int64_t r0 = row_at(lane & 31), r1 = row_at(32 + (lane & 31));
+    const uint4* A0 = codes + (r0 >> 6) * nchunk * 64 + (lane >> 5) * 64 + (r0 & 63);
+    const uint4* A1 = SAMPLE ? codes + (r1 >> 6) * nchunk * 64 + (lane >> 5) * 64 + (r1 & 63) : A0 + 32;
     const int nsteps = nchunk >> 1;
     // a sample pass has few blocks: its halves are workgroups of their own
     const int ub = SAMPLE ? static_cast<int>(blockIdx.y) * NQS : 0;
@@ -358,8 +377,8 @@ __global__ __launch_bounds__(256) void k_scan_mfma(
         for (int u = 0; u < NQS; ++u) acc[t][u] = v16i{};
 #pragma unroll 2
     for (int s = 0; s < nsteps; ++s) {
-        const u32x4 a0 = load_nt(A + 2 * s * 64);
-        const u32x4 a1 = load_nt(A + 2 * s * 64 + 32);
+        const u32x4 a0 = load_nt(A0 + 2 * s * 64);
+        const u32x4 a1 = load_nt(A1 + 2 * s * 64);
         v4i va0, va1;
         __builtin_memcpy(&va0, &a0, 16);
         __builtin_memcpy(&va1, &a1, 16);
@@ -637,8 +656,8 @@ __global__ __launch_bounds__(256, 2) void k_scan_mfma_wide(
 // two or four, two with eight, or with four tiles of 32 steps) holds the query fragments of the first NQT - NG tiles for
 // every K step in LDS for the whole kernel; the last NG tiles are read from
 // global memory (L2-resident, shared by every workgroup) two steps ahead.
-// Each wavefront takes one 32-row half of a 64-row code block at a time and
-// computes all NQT tiles for it (NQT accumulators of 32 x 32): the LDS
+// Each wavefront takes one 32-row half of a 64-row code block (or 32 positions
+// of the sample) at a time and computes all NQT tiles for it (NQT accumulators of 32 x 32): the LDS
 // fragments of the next K step are read while the current one multiplies,
 // and its code fragments stream into a register ring P steps deep that runs
 // on into the next half-block, so the epilogue of one half-block overlaps
@@ -673,7 +692,7 @@ template <int NQT, int NG, int NS, int P, int W, bool SAMPLE>
 __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     const uint4* __restrict__ codes, const float* __restrict__ scale,
     const float* __restrict__ vnorm, const float* __restrict__ enorm,
-    const uint64_t* __restrict__ vis, int64_t nblocks, int32_t nchunk,
+    const uint64_t* __restrict__ vis, int64_t nblocks, int64_t nwaves, int32_t nchunk,
     const v4i* __restrict__ qfrag, const ScanQ* __restrict__ sq, int32_t nq, float gamma,
     ScanOut o) {
     constexpr int NL = NQT - NG;            // tiles whose fragments stay in LDS
@@ -711,22 +730,40 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     }
     __syncthreads();
     float* meta = s_meta + wave * 96;
-    const int64_t nhalves = 2 * (SAMPLE ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks);
-    auto block_of = [&](int64_t x) { return SAMPLE ? (x >> 1) * o.sample_stride : x >> 1; };
+    // the row of this lane in half-block x, or position 32 x + lane % 32 of the
+    // sample (the half's first row, or row 0, where there is none)
+    auto first_row = [&](int64_t x) {
+        if constexpr (!SAMPLE) return 32 * x;
+        const int64_t r = sample_row(32 * x, o.sample_stride);
+        return r < nblocks * 64 ? r : int64_t(0);
+    };
+    auto there = [&](int64_t x) { return !SAMPLE || sample_row(32 * x + (lane & 31), o.sample_stride) < nblocks * 64; };
+    auto row_of = [&](int64_t x) {
+        if constexpr (!SAMPLE) return 32 * x + (lane & 31);
+        return there(x) ? sample_row(32 * x + (lane & 31), o.sample_stride) : first_row(x);
+    };
+    const int64_t nhalves = 2 * nwaves;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * W;
     int64_t hb = static_cast<int64_t>(blockIdx.x) * W + wave;
     const __amdgpu_buffer_rsrc_t qrs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<v4i*>(qfrag), 0, 0x7fffffff, 0x00020000);
     const int32_t qf_off = lane * 16;
-    const int32_t code_off = ((lane >> 5) * 64 + (lane & 31)) * 16;
-    auto half_rsrc = [&](int64_t x) {   // codes of half-block x (32 rows of block block_of(x))
+    auto half_rsrc = [&](int64_t x) {   // codes from the block of the half's first row on
         return __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint4*>(codes + block_of(x) * nchunk * 64 + 32 * (x & 1)), 0, 0x7fffffff, 0x00020000);
+            const_cast<uint4*>(codes + (first_row(x) >> 6) * nchunk * 64 + (SAMPLE ? 0 : 32 * (x & 1))), 0, 0x7fffffff,
+            0x00020000);
+    };
+    // this lane's offset there (32 positions of the sample span 32 strides of
+    // rows, 1 / 4,096 of the codes)
+    auto half_off = [&](int64_t x) {
+        if constexpr (!SAMPLE) return ((lane >> 5) * 64 + (lane & 31)) * 16;
+        const int64_t r = row_of(x);
+        return static_cast<int32_t>((((r >> 6) - (first_row(x) >> 6)) * nchunk * 64 + (lane >> 5) * 64 + (r & 63)) * 16);
     };
     v4i a[P];                     // ring: slot s % P holds step s
     v4i g[2][NG > 0 ? NG : 1];    // global tiles, two steps ahead
-    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int s, v4i& dst) {
-        dst = __builtin_amdgcn_raw_buffer_load_b128(rs, code_off, s * 2048, 0);
+    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int32_t off, int s, v4i& dst) {
+        dst = __builtin_amdgcn_raw_buffer_load_b128(rs, off, s * 2048, 0);
     };
     auto load_g = [&](int s, v4i (&dst)[NG > 0 ? NG : 1]) {
 #pragma unroll
@@ -736,17 +773,18 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
     float sv0 = 0.0f, nv0 = 0.0f, nev0 = 0.0f;
     uint32_t vbits = 0;
     auto load_meta = [&](int64_t x) {
-        const int64_t row = block_of(x) * 64 + 32 * (x & 1) + (lane & 31);
+        const int64_t row = row_of(x);
         sv0 = scale[row];
         nv0 = vnorm[row];
         nev0 = enorm[row];
-        vbits = static_cast<uint32_t>(vis[block_of(x)] >> (32 * (x & 1)));
+        if constexpr (SAMPLE) vbits = static_cast<uint32_t>(__ballot(there(x) && ((vis[row >> 6] >> (row & 63)) & 1ull)));
+        else vbits = static_cast<uint32_t>(vis[x >> 1] >> (32 * (x & 1)));
     };
     if (hb < nhalves) {
         load_meta(hb);
         const __amdgpu_buffer_rsrc_t rs = half_rsrc(hb);
 #pragma unroll
-        for (int p = 0; p < P; ++p) load_a(rs, p, a[p]);
+        for (int p = 0; p < P; ++p) load_a(rs, half_off(hb), p, a[p]);
         if (NG > 0) {
             load_g(0, g[0]);
             load_g(1, g[1]);
@@ -757,6 +795,7 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
         const bool more = nxt < nhalves;
         const __amdgpu_buffer_rsrc_t rs_cur = half_rsrc(hb);
         const __amdgpu_buffer_rsrc_t rs_nxt = half_rsrc(more ? nxt : hb);
+        const int32_t off_cur = half_off(hb), off_nxt = half_off(more ? nxt : hb);
         // this half-block's metadata (invisible rows carry a NaN scale)
         const bool visible = (vbits >> (lane & 31)) & 1u;
         [[maybe_unused]] const uint32_t vcur = vbits;
@@ -795,8 +834,8 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
                 if (s + 2 < NS) load_g(s + 2, g[s & 1]);
                 else if (more) load_g(s + 2 - NS, g[s & 1]);
             }
-            if (s + P < NS) load_a(rs_cur, s + P, a[p]);
-            else if (more) load_a(rs_nxt, s + P - NS, a[p]);
+            if (s + P < NS) load_a(rs_cur, off_cur, s + P, a[p]);
+            else if (more) load_a(rs_nxt, off_nxt, s + P - NS, a[p]);
             __builtin_amdgcn_sched_barrier(0);   // keep each step's loads in its step
         }
         if (more) load_meta(nxt);
@@ -964,7 +1003,7 @@ static int cu_count() {
 // cannot get its LDS.  EAHR_MFMA_KERNEL=wide (testing) keeps the older
 // kernel.
 template <int NQT, int NG, int NS, int P, int W, bool SAMPLE>
-static bool r1_launch(const IndexView& ix, const uint64_t* vis, int64_t nblocks, const v4i* qfrag,
+static bool r1_launch(const IndexView& ix, const uint64_t* vis, int64_t nblocks, int64_t nwaves, const v4i* qfrag,
                       const ScanQ* sq, int32_t nq, float gamma, const ScanOut& o, hipStream_t stream) {
     if (ix.nchunk / 2 != NS) return false;
     if (const char* e = std::getenv("EAHR_MFMA_KERNEL"))
@@ -980,11 +1019,11 @@ static bool r1_launch(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
         if (e != hipSuccess) (void)hipGetLastError();
     }
     if (ready.load() < 0) return false;
-    const int64_t halves = 2 * (SAMPLE ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks);
+    const int64_t halves = 2 * nwaves;
     const int64_t groups = (halves + W - 1) / W;
     const uint32_t g = static_cast<uint32_t>(std::min<int64_t>(groups, cu_count()));
     hipLaunchKernelGGL((k_scan_mfma_r1<NQT, NG, NS, P, W, SAMPLE>), dim3(g), dim3(64 * W), lds, stream, ix.codes, ix.scale,
-                       ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qfrag, sq, nq, gamma, o);
+                       ix.vnorm, ix.enorm, vis, nblocks, nwaves, ix.nchunk, qfrag, sq, nq, gamma, o);
     return true;
 }
 
@@ -992,11 +1031,11 @@ template <int NQT>
 static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks, const v4i* qfrag,
                       const ScanQ* sq, int32_t nq, float gamma, bool sample, const ScanOut& o,
                       hipStream_t stream) {
-    const int64_t waves = sample ? (nblocks + o.sample_stride - 1) / o.sample_stride : nblocks;
+    const int64_t waves = sample ? sample_blocks(nblocks, o.sample_stride) : nblocks;
     const uint32_t grid = static_cast<uint32_t>((waves + 3) / 4);
     auto r1 = [&](auto sample_c) {
         constexpr bool S = decltype(sample_c)::value;
-#define PVS_R1(NG, NS, P, W) r1_launch<NQT, NG, NS, P, W, S>(ix, vis, nblocks, qfrag, sq, nq, gamma, o, stream)
+#define PVS_R1(NG, NS, P, W) r1_launch<NQT, NG, NS, P, W, S>(ix, vis, nblocks, waves, qfrag, sq, nq, gamma, o, stream)
         // tiles in L2, K steps, ring depth, wavefronts per workgroup; the
         // query fragments of d = 1,024 leave no room for eight tiles.  9-32
         // queries on 1M x 384 take 76 us (5.1 TB/s), on one wavefront per
@@ -1015,7 +1054,7 @@ static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
     if (sample ? r1(std::true_type{}) : r1(std::false_type{})) return;
     if (sample) {
         hipLaunchKernelGGL((k_scan_mfma<NQT, true>), dim3(grid, NQT > 4 ? NQT / 4 : 1), dim3(256), 0, stream, ix.codes,
-                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qfrag, sq, nq,
+                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, waves, ix.nchunk, qfrag, sq, nq,
                            gamma, o);
     } else if (NQT >= 4) {
         constexpr int W = NQT >= 4 ? NQT : 4;
@@ -1042,7 +1081,7 @@ static void mfma_pass(const IndexView& ix, const uint64_t* vis, int64_t nblocks,
                                gamma, o);
     } else {
         hipLaunchKernelGGL((k_scan_mfma<NQT, false>), dim3(grid), dim3(256), 0, stream, ix.codes,
-                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, ix.nchunk, qfrag, sq, nq,
+                           ix.scale, ix.vnorm, ix.enorm, vis, nblocks, waves, ix.nchunk, qfrag, sq, nq,
                            gamma, o);
     }
 }

@@ -43,7 +43,7 @@ void launch_popcount(const uint64_t* v, int64_t words, unsigned long long* out, 
 }
 static void scan(int64_t nblocks, const ScanQ* sq, int32_t nq, bool sample, const ScanOut& o) {
     queued({{sq, nq * sizeof(ScanQ)}});
-    if (sample) queued({{o.sample, ((nq - 1) * o.sample_ld + (nblocks + o.sample_stride - 1) / o.sample_stride * 64) * 4}});
+    if (sample) queued({{o.sample, ((nq - 1) * o.sample_ld + sample_blocks(nblocks, o.sample_stride) * 64) * 4}});
     else queued({{o.pairs, o.pair_sub * kSub * sizeof(uint4)}, {o.pair_cnt, kSub * kCntStride * 4}, {o.q_evals, kSub * nq * 4}});
 }
 void launch_scan(const IndexView&, const uint64_t*, int64_t nb, const int8_t*, const ScanQ* sq, int32_t nq, float, bool s,

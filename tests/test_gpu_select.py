@@ -71,3 +71,71 @@ def test_selection_scale_extremes():
         x = (rng.standard_normal((6000, 32)) * rs).astype(np.float32)
         q = (rng.standard_normal((3, 32)) * qs).astype(np.float32)
         _check(E, x, q, 200, 6 * (6000 // 16))
+
+
+@pytest.fixture(scope="module", params=[64, 384, 512, 768, 1024])
+def sampled_index(request):
+    """Rows of which every second run is sampled, a tenth of them deleted."""
+    import torch
+    from paper_2608_07152_amd import eahr as E
+    d, n = request.param, 270_001
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    x = torch.randn(n, d, device="cuda", generator=g)
+    idx = E.pvs_build(x)
+    E.pvs_delete(idx, torch.randperm(n, device="cuda", generator=g)[: n // 10].cpu().numpy())
+    e = E.pvs_snapshot(idx)
+    yield E, idx, e, torch.randn(256, d, device="cuda", generator=g)
+    E.pvs_free(idx)
+
+
+@pytest.mark.parametrize("B", [9, 32, 40, 100, 200, 256])
+def test_the_sample_passes_agree(sampled_index, monkeypatch, B):
+    """The dot4 and the MFMA sample passes keep the same codes, so tau and with
+    it every count of the scans is the same: one, two, four and eight tiles of
+    the single-pass kernel (d = 384 up) and of the block kernel (d = 64); a
+    first scan, and one past the certified ranks."""
+    E, idx, e, q = sampled_index
+
+    def counts(path):
+        monkeypatch.setenv("EAHR_SCAN_PATH", path)
+        st = E.pvs_open(idx, q[:B].contiguous(), e)
+        out = []
+        for m in (100, 12_000):
+            E.pvs_next(st, m)
+            s = E.pvs_stats(st)
+            out.append({k: s[k] for k in ("scans", "candidates", "certified", "rescans", "overflows")})
+        E.pvs_close(st)
+        return out
+
+    counts("mfma")   # whatever the index expects of its readers, for both alike
+    got, want = counts("mfma"), counts("gemv")
+    assert got == want
+    assert got[0]["candidates"] > 0 and got[1]["scans"] > got[0]["scans"] > 0
+
+
+@pytest.mark.parametrize("n,d", [(4_000_000, 16), (1_200_000, 384)])
+def test_neighbours_stored_side_by_side_take_one_scan(n, d):
+    """Near-duplicates next to each other: the rows asked for fall into the
+    sample by whole runs, and the request still takes one scan."""
+    import torch
+    from paper_2608_07152_amd import eahr as E
+    B, m = 256, 100
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    centers = torch.randn(n // m, d, device="cuda", generator=g)
+    centers /= centers.norm(dim=1, keepdim=True)
+    x = centers.repeat_interleave(m, dim=0)
+    x += 1e-3 * torch.randn(n, d, device="cuda", generator=g)
+    idx = E.pvs_build(x)
+    del x
+    for _ in range(3):
+        pick = torch.randperm(n // m, device="cuda", generator=g)[:B]
+        st = E.pvs_open(idx, centers[pick].contiguous())
+        ids, _, cnt, _ = E.pvs_next(st, m)
+        assert list(cnt) == [m] * B
+        assert np.array_equal(np.sort(ids, axis=1), pick.cpu().numpy()[:, None] * m + np.arange(m))
+        s = E.pvs_stats(st)
+        E.pvs_close(st)
+        assert s["scans"] == 1 and s["rescans"] == 0, s
+    E.pvs_free(idx)
