@@ -819,6 +819,12 @@ static int64_t lower_overlap(const pvs_state* st, int32_t b) {
     return a;
 }
 
+// Ranks that the second scan of a query that reads on aims to have certified
+// after it: what a deep first scan would have, or some times the depth reached.
+static int64_t second_depth(const pvs_state::Query& Q, int32_t m) {
+    return std::max({pvs::kSpecSecond * (Q.emitted + m), pvs::kSpecFactor * Q.first, pvs::kSpecFloor});
+}
+
 // Exhaustive float32 generator: every visible row of the epoch is scored in
 // float32 (the same authoritative order as rescoring), each query's keys are
 // sorted once and the whole ranking becomes its certified cache, so the
@@ -960,12 +966,16 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         const int64_t have = static_cast<int64_t>(Q.cache.size());
         const int64_t avail = have - Q.emitted;
         const int64_t need = std::max<int64_t>(1, m - avail);
-        const int64_t factor = !st->reads_on && Q.scans == 1 ? pvs::kSpecSecond : pvs::kSpecFactor;
-        const int64_t depth = !st->reads_on && Q.scans == 0
-                            ? ahead / nq
-                            : std::max({factor * (Q.emitted + m), pvs::kSpecFloor, floor_all / nq}) - have;
+        const int64_t depth =
+            !st->reads_on && Q.scans == 0 ? ahead / nq
+            : std::max(!st->reads_on && Q.scans == 1 ? second_depth(Q, m)
+                                                     : std::max(pvs::kSpecFactor * (Q.emitted + m), pvs::kSpecFloor),
+                       floor_all / nq) - have;
         const int64_t spec = st->spec_off ? 0 : std::min(depth, pvs::kSpecBudget / nq);
-        if (Q.scans == 0) Q.shallow = std::max({need, mmin, std::min(ahead, pvs::kSpecBudget) / nq});
+        if (Q.scans == 0) {
+            Q.first = m;
+            Q.shallow = std::max({need, mmin, std::min(ahead, pvs::kSpecBudget) / nq});
+        }
         const int64_t overlap = lower_overlap(st, b);
         const int64_t target = std::max({need, mmin, spec}) + overlap;
         const double nf = static_cast<double>(need + overlap) * frac;
@@ -1225,7 +1235,6 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         }
         Q.cap_hint = 0;
         const int64_t c = h_cert[i];
-        Q.scans += c > 0;
         st->stats.certified += c;
         if (c > 0) {
             const uint64_t last = st->h_packed[h_offs[i] + c - 1];
@@ -1237,8 +1246,10 @@ static int scan_round(pvs_state* st, std::vector<int32_t>& todo, int32_t m) {
         if (certified_count(Q) >= st->n_vis) {
             Q.cert_exhausted = true;
             Q.retries = 0;
+            Q.scans += 1;
         } else if (avail >= m) {
             Q.retries = 0;
+            Q.scans += 1;
         } else {
             Q.retries += 1;
             st->stats.rescans += 1;
@@ -1265,6 +1276,20 @@ static int next_ranks(pvs_state* st, int32_t m, const uint8_t* active, int64_t* 
         if (Q.scans > 0 && std::min(Q.emitted + m, st->n_vis) > Q.shallow && (st->reads_on || !served))
             st->read_past = true;
         if (!served) todo.push_back(b);
+    }
+    // The ranks of a shallow first scan run out at about the same time for all
+    // queries: the first of them that reads past takes the others along into
+    // its second scan.
+    bool second = false;
+    for (const int32_t b : todo) second |= st->q[b].scans == 1;
+    if (second && !st->reads_on) {
+        todo.clear();
+        for (int32_t b = 0; b < B; ++b) {
+            const auto& Q = st->q[b];
+            if ((active && !active[b]) || Q.failed || Q.cert_exhausted) continue;
+            const int64_t want = Q.scans == 1 ? std::max<int64_t>(Q.emitted + m, second_depth(Q, m)) : Q.emitted + m;
+            if (certified_count(Q) < want) todo.push_back(b);
+        }
     }
     for (int guard = 0; !todo.empty(); ++guard) {
         if (guard > 200) EAHR_FAIL(EAHR_E_HIP, "pvs_next: scan loop did not converge");

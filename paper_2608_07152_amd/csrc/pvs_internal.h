@@ -65,18 +65,29 @@ constexpr int64_t kTargetBudget = 8192;
 //
 // A caller that asks once pays for ranks nobody reads, one that reads on for
 // another scan.  So the first scan of a state certifies the request and about
-// min(2^17, rows / 16) ranks ahead over its queries (rescoring them costs at
-// most about an eighth of streaming the codes), unless its caller always
+// min(2^17, rows / 16) ranks ahead over its queries, unless its caller always
 // reads on (eahr_topk, merges: pvs_expect_depth) or one of the last two states
 // closed on the index read past what such a scan certifies (by ranks, not by
-// calls: short pages served by one scan do not count); the second scan takes
-// kSpecSecond in place of the factor.
-// Certified 16 requests ahead at once, 256 queries for 1,000 ranks on
-// 1M x 384 took 3,010 us and 256 for 100 on 8.8M x 768 4,950; as now 980 and
-// 2,910.  Never predicting that a caller reads on made 4 of 12 paging
-// programs slower than before (7 doubling pages of 640 for 64 queries on
-// 4M x 768: 15.8 instead of 12.4 ms).
-constexpr int64_t kSpecSecond = 4;
+// calls: short pages served by one scan do not count).  Their rescoring is not
+// free: it takes as long as the scan for 16 queries on 1M x 384 (72 and 78 us)
+// and 100 on 2M x 1,024 (370 and 375), and a fifth of it on 8.8M x 768 (283 and
+// 1,275 for one query, 416 and 2,101 for 256).  Certified 16 requests ahead at
+// once, 256 queries for 1,000 ranks on 1M x 384 took 3,010 us and 256 for 100 on
+// 8.8M x 768 4,950; as now 1,004 and 2,980.
+//
+// A state that reads on unpredicted takes a second scan, for all of its queries
+// together (they would need one at this request or the next), which certifies
+// up to what a deep first scan would have, or kSpecSecond times the depth
+// reached: so it pays for one shallow scan more than with a deep first scan.
+// Doubling pages, us in the first such state on an index / in later ones / with
+// every first scan deep, before these rules: 4M x 768, 64 queries, seven pages
+// from 640 12,940 / 12,110 / 13,530, four pages 3,750 / 2,780 / 3,130; 256
+// queries, four pages from 100 6,090 / 4,110 / 5,190; 1M x 384, 64 queries, five
+// from 640 5,060 / 4,640 / 7,950; 50K x 128, 32 queries, five from 50 626 / 475 /
+// 674.  A second scan for each query as it ran out, four times the depth
+// reached, took up to 14,260 us where a deep first scan took 5,000 (256 queries,
+// five pages from 100 on 4M x 768; now 6,500).
+constexpr int64_t kSpecSecond = 2;
 constexpr int64_t kSpecFactor = 16;
 constexpr int64_t kSpecBudget = int64_t(1) << 22;
 constexpr int64_t kSpecFloor = 4096;
@@ -203,7 +214,8 @@ struct pvs_state {
         bool failed = false;
         bool cert_exhausted = false;    // every visible row certified
         int retries = 0;                // consecutive scans that certified too few
-        int scans = 0;                  // scans that certified ranks for it
+        int scans = 0;                  // scans that served a request of it
+        int64_t first = 0;              // its first request
         int64_t shallow = 0;            // ranks that a shallow first scan aims at
         int64_t cap_hint = 0;           // candidate capacity needed by the last overflow
         int64_t evals = 0;              // (query, row) pairs rescored in float32

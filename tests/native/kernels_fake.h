@@ -1,6 +1,7 @@
 // Stand-ins for the dense channel's kernels on the CPU: they check that their
 // buffers are live and large enough, and rank the rows of an index by id.  A
-// scan certifies every row, or with g_by_k the next k rows of each query.
+// scan certifies every row, or with g_by_k the next k rows of each query (with
+// g_spread a percentage fewer for each query after the first).
 #pragma once
 #include <cstring>
 #include <initializer_list>
@@ -15,10 +16,12 @@ namespace pvs {
 static uint64_t key_of(int64_t row) { return (static_cast<uint64_t>(~0x80000000u) << 32) | static_cast<uint64_t>(row); }
 static int64_t g_rows = 0;
 static bool g_by_k = false;
+static int64_t g_spread = 0;
 static int64_t first_of(const ScanQ& q) { return g_by_k && q.has_cert ? q.id_cert + 1 : 0; }
 static int64_t count_of(const ScanQ& q) {
     const int64_t left = g_rows - first_of(q);
-    return g_by_k && q.k < left ? q.k : left;
+    const int64_t k = q.k - q.k * q.qi * g_spread / 100;
+    return g_by_k && k < left ? k : left;
 }
 static void queued(std::initializer_list<std::pair<const void*, size_t>> bufs) {
     for (const auto& b : bufs) fake::expect(fake::inside(b.first, b.second), "a kernel was given a bad buffer");

@@ -1,7 +1,7 @@
 // How far ahead scans certify, on the CPU (kernels_fake.h: a scan certifies
 // the k ranks it is asked for): a caller that asks once is not made to pay for
 // ranks nobody reads by callers that do not need another scan either, and one
-// that reads on is served by one deep scan from its second state on.
+// that reads on is served by two scans, and by one from its second state on.
 #include <vector>
 
 #include "kernels_fake.h"
@@ -70,6 +70,13 @@ int main() {
     shallow("states that asked once did not end the deep scans");
     // past the end of the list, from one scan
     fake::expect(read(ix, {static_cast<int32_t>(kRows) - 1, 5, 5}).scans <= 2, "a whole list");
+    // the queries of a first state that reads on run out of certified ranks at
+    // different requests, and share their second scan
+    for (int i = 0; i < 3; ++i) read(ix, {20});
+    pvs::g_spread = 15;
+    const Read pages = read(ix, {400, 400, 400, 400, 400, 400});
+    fake::expect(pages.scans == 2, "queries that run out one after another take a scan each");
+    pvs::g_spread = 0;
     pvs_free(ix);
     // a collection that one shallow scan certifies whole
     pvs::g_rows = 200;
