@@ -25,11 +25,13 @@ namespace pvs {
 constexpr int64_t kSampleBlocks = 2048;
 // The request itself is certified with a margin on its count in the sample,
 // because falling short costs another scan.  Its rows may lie side by side, so
-// they are taken to fall into the sample by whole runs: four standard deviations
-// of a Poisson count of runs and one and a half runs more, which one query in
-// 10,000 exceeds where every run is full, and fewer anywhere else.
+// they are taken to fall into the sample by whole runs: three standard
+// deviations of a Poisson count of runs and one and a half runs more.  At worst,
+// with every run full, about one query in 1,000 exceeds that and is scanned
+// again; with four, every call of 256 queries for 1,000 ranks on 1M x 384 took
+// 1,005 us instead of 973.
 constexpr double kSampleMargin = 1.25;
-constexpr double kSampleSigmas = 4.0;
+constexpr double kSampleSigmas = 3.0;
 // Smallest candidate pool allocated for a scan, and the largest pool one scan
 // round may use (queries beyond it wait for the next round).
 constexpr int64_t kMinCap = 4096;
@@ -71,9 +73,9 @@ constexpr int64_t kTargetBudget = 8192;
 // calls: short pages served by one scan do not count).  Their rescoring is not
 // free: it takes as long as the scan for 16 queries on 1M x 384 (72 and 78 us)
 // and 100 on 2M x 1,024 (370 and 375), and a fifth of it on 8.8M x 768 (283 and
-// 1,275 for one query, 416 and 2,101 for 256).  Certified 16 requests ahead at
+// 1,210 for one query, 365 and 2,095 for 256).  Certified 16 requests ahead at
 // once, 256 queries for 1,000 ranks on 1M x 384 took 3,010 us and 256 for 100 on
-// 8.8M x 768 4,950; as now 1,004 and 2,980.
+// 8.8M x 768 4,950; as now 973 and 2,940.
 //
 // A state that reads on unpredicted takes a second scan, for all of its queries
 // together (they would need one at this request or the next), which certifies
