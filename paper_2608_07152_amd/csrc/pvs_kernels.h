@@ -18,8 +18,10 @@ constexpr int kMaxMfmaQueries = 256;  // queries per MFMA scan pass (8 tiles of 
 // covers this (kSampleSigmas) grows with the run's length: with whole blocks as
 // runs and a margin for independent rows, a request for neighbours stored side
 // by side took up to three scans.  Eight rows of one 16-byte chunk are a cache
-// line, so the sample is read as fast as whole blocks are; runs of four read
-// half lines (100 queries of 2M x 1,024: 128 us instead of 106).
+// line, so the sample is read about as fast as whole blocks are (the pass of
+// 100 queries of 2M x 1,024 with its selection 106 us and 105, the pass of 256
+// of 8.8M x 768 136 and 117); runs of four read half lines (128 us instead of
+// 106).
 constexpr int kSampleRun = 8;
 inline int64_t sample_runs(int64_t nblocks, int64_t stride) {
     return (nblocks * (kBlockRows / kSampleRun) + stride - 1) / stride;

@@ -842,8 +842,9 @@ __global__ __launch_bounds__(64 * W, 1) void k_scan_mfma_r1(
         if constexpr (SAMPLE) {
             // every pair's interval, four consecutive rows of a query in one
             // 16-byte store (a lane's accumulators 4 g .. 4 g + 3).  256
-            // queries of d = 768: 113 us for 2,048 blocks; one wavefront per
-            // block with two 4-byte stores a pair took 313 us.
+            // queries of d = 768: 113 us for 2,048 whole blocks (136 in runs of
+            // eight rows); one wavefront per block with two 4-byte stores a
+            // pair took 313 us.
             __builtin_amdgcn_wave_barrier();
             const int h4 = 4 * (lane >> 5);
             uint32_t* srow = o.sample + (hb >> 1) * 64 + 32 * (hb & 1) + h4;
