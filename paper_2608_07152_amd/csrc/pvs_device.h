@@ -124,11 +124,6 @@ __device__ __forceinline__ float scaled_threshold(float thr, float sq) {
     return (r > -INFINITY && r < INFINITY) ? r : -INFINITY;
 }
 
-// The row at position i of the sample; rows from 64 nblocks on do not exist.
-__device__ __forceinline__ int64_t sample_row(int64_t i, int64_t stride) {
-    return i / kSampleRun * stride * kSampleRun + i % kSampleRun;
-}
-
 // A sampled pair is kept as two 16-bit codes: the value tau is selected from
 // (lower bound or midpoint) in the low half, the upper bound in the high one.
 // A code is the value over a power of two of the query that puts the largest

@@ -16,7 +16,7 @@
 using KeyCache = std::vector<uint64_t, ::eahr::NoInit<uint64_t>>;
 
 namespace pvs {
-// Threshold estimation samples every stride-th run of kSampleRun rows, with the
+// Threshold estimation samples one in stride runs of kSampleRun rows, with the
 // largest stride that keeps at least this many blocks' worth of rows sampled.
 // With stride 1 tau is the target-th largest lower bound, so at least the
 // target is certified.  With a larger stride tau is taken from the sampled

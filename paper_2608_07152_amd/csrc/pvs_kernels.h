@@ -11,23 +11,30 @@ constexpr int kMaxDim = 4096;      // 127^2 * 4096 < 2^31 and a_m < 1
 constexpr int kSortTile = 2048;    // keys merged per workgroup
 constexpr int kMaxGemvQueries = 8; // queries per GEMV scan pass
 constexpr int kMaxMfmaQueries = 256;  // queries per MFMA scan pass (8 tiles of 32)
-// The sample is drawn in runs of kSampleRun consecutive rows: position i of it
-// is row sample_row(i, stride), and there are sample_blocks(...) * 64 positions,
-// those at the end possibly past the last row.  Rows stored by topic or with
-// near-duplicates side by side fall into it by whole runs, and the margin that
-// covers this (kSampleSigmas) grows with the run's length: with whole blocks as
-// runs and a margin for independent rows, a request for neighbours stored side
-// by side took up to three scans.  Eight rows of one 16-byte chunk are a cache
-// line, so the sample is read about as fast as whole blocks are (the pass of
-// 100 queries of 2M x 1,024 with its selection 106 us and 105, the pass of 256
-// of 8.8M x 768 136 and 117); runs of four read half lines (128 us instead of
-// 106).
+// The sample is drawn in runs of kSampleRun consecutive rows, one from every
+// `stride` runs: position i of it is row sample_row(i, stride), and there are
+// sample_blocks(...) * 64 positions, those at the end possibly past the last row.
+// Which run of each `stride` follows the multiples of the golden section, so
+// that rows stored in turn from several sources, whatever their number, are
+// sampled alike.  Rows stored by topic or with near-duplicates side by side fall
+// into the sample by whole runs, and the margin that covers this (kSampleSigmas)
+// grows with the run's length: with whole blocks as runs and a margin for
+// independent rows, a request for neighbours stored side by side took up to
+// three scans.  Eight rows of one 16-byte chunk are a cache line, so the sample
+// is read about as fast as whole blocks are (the pass of 100 queries of
+// 2M x 1,024 with its selection 106 us and 105, the pass of 256 of 8.8M x 768
+// 136 and 117); runs of four read half lines (128 us instead of 106).
 constexpr int kSampleRun = 8;
 inline int64_t sample_runs(int64_t nblocks, int64_t stride) {
     return (nblocks * (kBlockRows / kSampleRun) + stride - 1) / stride;
 }
 inline int64_t sample_blocks(int64_t nblocks, int64_t stride) {
     return (sample_runs(nblocks, stride) + kBlockRows / kSampleRun - 1) / (kBlockRows / kSampleRun);
+}
+__host__ __device__ inline int64_t sample_row(int64_t i, int64_t stride) {
+    const uint64_t s = static_cast<uint64_t>(i) / kSampleRun;
+    const uint64_t r = static_cast<uint64_t>(static_cast<uint32_t>(s) * 0x9e3779b9u) * static_cast<uint64_t>(stride) >> 32;
+    return static_cast<int64_t>((s * stride + r) * kSampleRun) + i % kSampleRun;
 }
 // The candidate pool of a scan is split into kSub sub-regions, each with its
 // own append counter; the code block (or workgroup) picks the sub-region

@@ -2,7 +2,7 @@
 // Int8 codes are streamed once per scan; each (query, row) pair gets its exact
 // integer dot product and its score interval (pvs_device.h), and rows whose
 // interval can reach the query's threshold tau are appended to the query's
-// candidate region.  A sample pass over every sample_stride-th run of rows
+// candidate region.  A sample pass over one in sample_stride runs of rows
 // records the bounds from which tau is selected.
 //
 // Two kernels compute the same integers: a dot4 GEMV for a few queries and an

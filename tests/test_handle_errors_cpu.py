@@ -42,3 +42,7 @@ def test_sparse_channel_beside_kept_memory(tmp_path):
 
 def test_how_far_ahead_scans_certify(tmp_path):
     _run(tmp_path, "reading_on.cpp", ["pvs_api.cpp", "dev_pool.cpp", "errors.cpp"])
+
+
+def test_rows_of_the_threshold_sample(tmp_path):
+    _run(tmp_path, "sample_rows.cpp", [])
